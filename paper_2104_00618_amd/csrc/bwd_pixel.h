@@ -294,23 +294,17 @@ struct LevelGeom {
 };
 
 __device__ __forceinline__ LevelGeom level_geom(const LevelTable& T, int l, df Ux, df Uy, df Uz) {
-    const float top = T.top[l];
-    const int lnb = T.lnb[l];
+    const LevelRow R = T.row[l];
     const float sc = __int_as_float((127 - l) << 23);   // 2^-l
-    const Axis ax = axis_taps(Ux, sc, top);
-    const Axis ay = axis_taps(Uy, sc, top);
-    const Axis az = axis_taps(Uz, sc, top);
-    // brick layout: ((bz * nb + by) * nb + bx) * 64 + (z & 3) * 16 + (y & 3) * 4 + (x & 3), nb = 2^lnb
-    const uint32_t cx0 = ((ax.i0 >> 2) << 6) | (ax.i0 & 3), cx1 = ((ax.i1 >> 2) << 6) | (ax.i1 & 3);
-    const uint32_t cy0 = ((ay.i0 >> 2) << (6 + lnb)) | ((ay.i0 & 3) << 2);
-    const uint32_t cy1 = ((ay.i1 >> 2) << (6 + lnb)) | ((ay.i1 & 3) << 2);
-    const uint32_t cz0 = ((az.i0 >> 2) << (6 + 2 * lnb)) | ((az.i0 & 3) << 4);
-    const uint32_t cz1 = ((az.i1 >> 2) << (6 + 2 * lnb)) | ((az.i1 & 3) << 4);
+    const Axis ax = axis_taps(Ux, sc, R.top);
+    const Axis ay = axis_taps(Uy, sc, R.top);
+    const Axis az = axis_taps(Uz, sc, R.top);
+    const uint32_t x0 = brick_x(ax.i0), y0 = brick_y(ay.i0, R.sy), z0 = brick_z(az.i0, R.sz);
     LevelGeom g;
-    g.base = T.off[l] + cx0 + cy0 + cz0;
-    g.dx = cx1 - cx0;
-    g.dy = cy1 - cy0;
-    g.dz = cz1 - cz0;
+    g.base = R.off + z0 + y0 + x0;
+    g.dx = brick_x(ax.i1) - x0;
+    g.dy = brick_y(ay.i1, R.sy) - y0;
+    g.dz = brick_z(az.i1, R.sz) - z0;
     g.wx = ax.w1;
     g.wy = ay.w1;
     g.wz = az.w1;
@@ -332,9 +326,9 @@ template <int DT, bool SPLIT = false>
 __device__ __forceinline__ float4 gather_geom(const TraceArgs& a, const LevelGeom& g) {
     const float wx0 = 1.0f - g.wx, wy0 = 1.0f - g.wy, wz0 = 1.0f - g.wz;
     const float wxy[4] = {wx0 * wy0, g.wx * wy0, wx0 * g.wy, g.wx * g.wy};
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 s = first_tap(wxy[0] * wz0, vct_fetch_texel<DT>(a.rsrc, g.base));
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 1; q < 8; ++q) {
         const uint32_t idx = g.base + ((q & 1) ? g.dx : 0u) + ((q & 2) ? g.dy : 0u) + ((q & 4) ? g.dz : 0u);
         acc_tap(s, wxy[q & 3] * ((q & 4) ? g.wz : wz0), vct_fetch_texel<DT>(a.rsrc, idx));
         if (SPLIT && (DT & ~VCT_WIDE) == VCT_F32 && q == 3) __builtin_amdgcn_sched_barrier(0);
@@ -352,24 +346,19 @@ __device__ __forceinline__ float4 gather_geom(const TraceArgs& a, const LevelGeo
 template <int DT>
 __device__ __forceinline__ float4 gather_geom_shared(const TraceArgs& a, const LevelGeom& g) {
     if constexpr (DT == VCT_F32) {
-        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.base);
-        const uint32_t dx = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dx);
-        const uint32_t dy = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dy);
-        const uint32_t dz = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dz);
-        if (VCT_WAVE_AGREES(g.base != b0 || g.dx != dx || g.dy != dy || g.dz != dz)) {
+        const uint32_t last = g.base + g.dx + g.dy + g.dz;
+        const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.base);
+        const uint32_t i7 = (uint32_t)__builtin_amdgcn_readfirstlane((int)last);
+        if (VCT_WAVE_AGREES(((g.base ^ i0) | (last ^ i7)) != 0u)) {
             const float wx0 = 1.0f - g.wx, wy0 = 1.0f - g.wy, wz0 = 1.0f - g.wz;
             const float wxy[4] = {wx0 * wy0, g.wx * wy0, wx0 * g.wy, g.wx * g.wy};
-            const vct_v4i rs = vct_rebase_raw(a.rraw, (uint64_t)b0 * 16u);
-            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            float4 v[8];
+            scalar_texels(a.rraw, i0, (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dx),
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dy),
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)g.dz), v);
+            float4 s = first_tap(wxy[0] * wz0, v[0]);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t step = ((q & 1) ? dx : 0u) + ((q & 2) ? dy : 0u) + ((q & 4) ? dz : 0u);
-                VCT_CHECK_TEXEL(b0 + step);
-                const vct_v4i v = vct_scalar_load_v4i32(rs, (int32_t)(step * 16u), 0);
-                acc_tap(s, wxy[q & 3] * ((q & 4) ? g.wz : wz0),
-                        make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z),
-                                    __int_as_float(v.w)));
-            }
+            for (int q = 1; q < 8; ++q) acc_tap(s, wxy[q & 3] * ((q & 4) ? g.wz : wz0), v[q]);
             return s;
         }
     }
