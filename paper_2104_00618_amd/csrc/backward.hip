@@ -223,29 +223,43 @@ __device__ __forceinline__ float bfly8(const float wp[8], const float wpart[4], 
     return sum32(sum16(r[0]));
 }
 
-// The lane's slot-ordered weights of one level's 8 taps, level weight wl
-// folded in (an axis that clamps has both taps on one texel, each with its
-// own weight).
-__device__ __forceinline__ void emit_weights(const LevelGeom& g, float wl, const EmitLane& e, float wp[8]) {
-    const float x0 = 1.0f - g.wx, y0 = 1.0f - g.wy, z0 = 1.0f - g.wz;
-    const float xa = e.xf ? g.wx : x0, xb = e.xf ? x0 : g.wx;
-    const float ya = e.yf ? g.wy : y0, yb = e.yf ? y0 : g.wy;
-    const float za = e.zf ? g.wz : z0, zb = e.zf ? z0 : g.wz;
+// The lane's slot-ordered weights of one level's 8 taps, level weight wl folded in.
+__device__ __forceinline__ void emit_weights(float wx, float wy, float wz, float wl, const EmitLane& e, float wp[8]) {
+    const float x0 = 1.0f - wx, y0 = 1.0f - wy, z0 = 1.0f - wz;
+    const float xa = e.xf ? wx : x0, xb = e.xf ? x0 : wx;
+    const float ya = e.yf ? wy : y0, yb = e.yf ? y0 : wy;
+    const float za = wl * (e.zf ? wz : z0), zb = wl * (e.zf ? z0 : wz);
     const float wxy[4] = {xa * ya, xb * ya, xa * yb, xb * yb};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) wp[k] = wl * (wxy[k & 3] * ((k >> 2) ? zb : za));
+    for (int k = 0; k < 8; ++k) wp[k] = wxy[k & 3] * ((k >> 2) ? zb : za);
+}
+
+// Upper-tap weights of a footprint for the scatter: an axis that clamps has both
+// its taps on the lower texel, which then gets all the weight.  So the footprint
+// is known by its base texel alone, and the steps to its neighbours follow from
+// that texel's place in its brick (level of side 2^lgn >> level); past an axis that
+// clamps they lead out of the level, but only sums of zeros would go there.
+__device__ __forceinline__ void inner_weights(const LevelGeom& g, float& ex, float& ey, float& ez) {
+    ex = g.dx != 0u ? g.wx : 0.f;
+    ey = g.dy != 0u ? g.wy : 0.f;
+    ez = g.dz != 0u ? g.wz : 0.f;
+}
+
+__device__ __forceinline__ void key_steps(uint32_t key, int level, int lgn, uint32_t& dx, uint32_t& dy, uint32_t& dz) {
+    const int lnb = max(lgn - level - 2, 0);
+    dx = (key & 3u) == 3u ? 61u : 1u;
+    dy = (key & 12u) == 12u ? (64u << lnb) - 12u : 4u;
+    dz = (key & 48u) == 48u ? (64u << (2 * lnb)) - 48u : 16u;
 }
 
 // A group's fixed-point values held back while the wave's next samples on the
-// same level parity fall on the same footprint (same base texel and clamp
-// pattern): they are summed in registers and added to the accumulator once.
+// same level parity fall on the same footprint (base texel): they are summed in registers and added to the accumulator once.
 // Integer addition is associative, so the accumulator ends bitwise the same
-// as with one atomic per sample.  The key and the index steps are
-// wave-uniform; qv is the lane's value (zero outside the emitting lanes).
+// as with one atomic per sample.  The key and the level are wave-uniform; qv
+// is the lane's value (zero outside the emitting lanes).
 struct Held {
     uint32_t key;          // base texel, kNoKey when empty
-    int kc;                // clamp pattern
-    uint32_t dx, dy, dz;   // index steps of the footprint
+    int level;
     long long qv;
 };
 constexpr uint32_t kNoKey = 0xffffffffu;
@@ -254,61 +268,68 @@ constexpr uint32_t kNoKey = 0xffffffffu;
 // (coarse levels) or to the global accumulator.
 __device__ __forceinline__ void add_fixed(uint32_t idx, int ch, long long qv, unsigned long long* __restrict__ acc,
                                           unsigned long long* small, uint32_t small_off) {
-    VCT_CHECK_ACC(idx);
+    if (qv != 0) {
+        VCT_CHECK_ACC(idx);
+    }
     if (qv != 0 && idx >= small_off) atomicAdd(&small[(idx - small_off) * 4 + ch], (unsigned long long)qv);
     if (qv != 0 && idx < small_off) atomicAdd(&acc[(size_t)idx * 4 + ch], (unsigned long long)qv);
 }
 
-__device__ __forceinline__ void flush_held(Held& h, const EmitLane& e, int ch, unsigned long long* __restrict__ acc,
-                                           unsigned long long* small, uint32_t small_off) {
-    if (h.key != kNoKey)
-        add_fixed(h.key + (h.dx & e.xm) + (h.dy & e.ym) + (h.dz & e.zm), ch, h.qv, acc, small, small_off);
+// What a wave scatters to.
+struct Scatter {
+    unsigned long long* acc;      // global accumulator
+    unsigned long long* small;    // the workgroup's LDS table of the texels from small_off on
+    uint32_t small_off;
+    int E, lgn, lane;
+};
+
+__device__ __forceinline__ void add_footprint(const Scatter& t, const EmitLane& e, uint32_t key, int level, uint32_t delta,
+                                              int ch, long long qv) {
+    uint32_t dx, dy, dz;
+    key_steps(key, level, t.lgn, dx, dy, dz);
+    add_fixed(key + delta + (dx & e.xm) + (dy & e.ym) + (dz & e.zm), ch, qv, t.acc, t.small, t.small_off);
+}
+
+__device__ __forceinline__ void flush_held(const Scatter& t, Held& h, const EmitLane& e, int ch) {
+    if (h.key != kNoKey) add_footprint(t, e, h.key, h.level, 0u, ch, h.qv);
     h.key = kNoKey;
 }
 
-__device__ __forceinline__ void hold(Held& h, uint32_t k, int kc, uint32_t dx, uint32_t dy, uint32_t dz, long long qv,
-                                     const EmitLane& e, int ch, unsigned long long* __restrict__ acc,
-                                     unsigned long long* small, uint32_t small_off) {
-    if (h.key == k && h.kc == kc) {
+__device__ __forceinline__ void hold(const Scatter& t, Held& h, uint32_t k, int level, long long qv, const EmitLane& e,
+                                     int ch) {
+    if (h.key == k) {
         h.qv += qv;
         return;
     }
-    flush_held(h, e, ch, acc, small, small_off);
+    flush_held(t, h, e, ch);
     h.key = k;
-    h.kc = kc;
-    h.dx = dx;
-    h.dy = dy;
-    h.dz = dz;
+    h.level = level;
     h.qv = qv;
 }
 
 // The group loop of one level's emission.  Lanes whose samples share the
-// same base texel and clamp pattern have the same 8 taps; each such group is
-// summed across the wave (fixed order), after which 32 lanes (8 for alpha
-// only) hold its taps x channels.  sink(k, kc, lev, dx, dy, dz, sum, emitter,
-// ch) receives each group: its base texel, clamp pattern, level and index
-// steps (wave-uniform), the lane's sum, whether the lane emits it, and its
+// same base texel have the same 8 taps; each such group is summed across the
+// wave (fixed order), after which 32 lanes (8 for alpha only) hold its taps x
+// channels.  sink(k, lev, sum, emitter, ch) receives each group: its base texel
+// and level (wave-uniform), the lane's sum, whether the lane emits it, and its
 // channel.
 template <bool ALPHA_ONLY, typename Sink>
 __device__ __forceinline__ void emit_groups(bool live, const LevelGeom& geo, float wl, const float gs[4],
                                             const EmitLane& e, int lane, Sink&& sink) {
     unsigned long long mask = __ballot(live);
     if (mask == 0) return;   // (wave-uniform: no lane emits on this level)
-    float wp[8];
-    emit_weights(geo, wl, e, wp);
+    float ex, ey, ez, wp[8];
+    inner_weights(geo, ex, ey, ez);
+    emit_weights(ex, ey, ez, wl, e, wp);
     float wpart[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) wpart[k] = dpp<kDppXor15>(wp[k + 4]);
-    const uint32_t key = live ? geo.base : 0xffffffffu;
-    const int kcl = (geo.dx == 0 ? 1 : 0) | (geo.dy == 0 ? 2 : 0) | (geo.dz == 0 ? 4 : 0);
     const bool emitter = ALPHA_ONLY ? ((lane & 0x31) == 0) : (lane < 32);
     const int ch = ALPHA_ONLY ? 3 : e.ch;
     while (mask) {
         const int leader = __builtin_ctzll(mask);
-        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key, leader);
-        const int kc = __builtin_amdgcn_readlane(kcl, leader);
-        const bool in = live && key == k && kcl == kc;
-        const unsigned long long gm = __ballot(in);
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)geo.base, leader);
+        const bool in = live && geo.base == k;
         float sum;
         if (ALPHA_ONLY) {
             sum = bfly8(wp, wpart, in ? gs[3] : 0.f);
@@ -318,37 +339,24 @@ __device__ __forceinline__ void emit_groups(bool live, const LevelGeom& geo, flo
             for (int m = 0; m < 4; ++m) g[m] = in ? gs[m] : 0.f;
             sum = bfly32(wp, wpart, g);
         }
-        const int lev = __builtin_amdgcn_readlane(geo.level, leader);
-        const uint32_t dx = (uint32_t)__builtin_amdgcn_readlane((int)geo.dx, leader);
-        const uint32_t dy = (uint32_t)__builtin_amdgcn_readlane((int)geo.dy, leader);
-        const uint32_t dz = (uint32_t)__builtin_amdgcn_readlane((int)geo.dz, leader);
-        sink(k, kc, lev, dx, dy, dz, sum, emitter, ch);
-        mask &= ~gm;
+        sink(k, __builtin_amdgcn_readlane(geo.level, leader), sum, emitter, ch);
+        mask &= ~__ballot(in);
     }
 }
 
-// Emit one level's tap gradients of the wave as fixed-point integers: to the
-// workgroup's LDS table for the coarse levels (side <= 8), to the global
-// accumulator otherwise.
-template <bool ALPHA_ONLY, bool HOLD = false>
-__device__ __forceinline__ void emit_level(bool live, const LevelGeom& geo, float wl, const float gs[4],
-                                           const EmitLane& e, int E, int lev_shift,
-                                           unsigned long long* __restrict__ acc, unsigned long long* small,
-                                           uint32_t small_off, int lane, Held* held = nullptr) {
-    emit_groups<ALPHA_ONLY>(live, geo, wl, gs, e, lane,
-                            [&](uint32_t k, int kc, int lev, uint32_t dx, uint32_t dy, uint32_t dz, float sum,
-                                bool emitter, int ch) {
-        const long long qv = emitter ? fixed_point(sum, E - lev_shift * lev) : 0;
-        if constexpr (HOLD) {
-            // (the two levels of a sample differ in parity, and a level keeps
-            // its parity stream as the march moves up)
-            if (lev & 1)
-                hold(held[1], k, kc, dx, dy, dz, qv, e, ch, acc, small, small_off);
-            else
-                hold(held[0], k, kc, dx, dy, dz, qv, e, ch, acc, small, small_off);
-        } else {
-            add_fixed(k + (dx & e.xm) + (dy & e.ym) + (dz & e.zm), ch, qv, acc, small, small_off);
-        }
+// Isotropic pyramids: level l's integers carry the scale 2^(E - 3l) (the 1/8 per
+// level of the mip adjoint folded in).
+template <bool ALPHA_ONLY>
+__device__ __forceinline__ void emit_level(const Scatter& t, bool live, const LevelGeom& geo, float wl, const float gs[4],
+                                           const EmitLane& e, Held* held) {
+    emit_groups<ALPHA_ONLY>(live, geo, wl, gs, e, t.lane, [&](uint32_t k, int lev, float sum, bool emitter, int ch) {
+        const long long qv = emitter ? fixed_point(sum, t.E - 3 * lev) : 0;
+        // (the two levels of a sample differ in parity, and a level keeps
+        // its parity stream as the march moves up)
+        if (lev & 1)
+            hold(t, held[1], k, lev, qv, e, ch);
+        else
+            hold(t, held[0], k, lev, qv, e, ch);
     });
 }
 
@@ -357,19 +365,14 @@ __device__ __forceinline__ void emit_level(bool live, const LevelGeom& geo, floa
 // signs): the three directions' sums are the axis-free sum times w_a^2, so
 // each group runs one butterfly and adds it at the three directions' offsets.
 template <bool ALPHA_ONLY>
-__device__ __forceinline__ void emit_level_dirs(bool live, const LevelGeom& geo, float wl, const float gs[4],
-                                                const EmitLane& e, int E, const float wt[3], const int dsel[3],
-                                                const DirTable* D, unsigned long long* __restrict__ acc,
-                                                unsigned long long* small, uint32_t small_off, int lane) {
-    emit_groups<ALPHA_ONLY>(live, geo, wl, gs, e, lane,
-                            [&](uint32_t k, int, int lev, uint32_t dx, uint32_t dy, uint32_t dz, float sum,
-                                bool emitter, int ch) {
-        const uint32_t tap = k + (dx & e.xm) + (dy & e.ym) + (dz & e.zm);
+__device__ __forceinline__ void emit_level_dirs(const Scatter& t, bool live, const LevelGeom& geo, float wl,
+                                                const float gs[4], const EmitLane& e, const float wt[3],
+                                                const int dsel[3], const DirTable* D) {
+    emit_groups<ALPHA_ONLY>(live, geo, wl, gs, e, t.lane, [&](uint32_t k, int lev, float sum, bool emitter, int ch) {
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             if (wt[ax] == 0.0f) continue;
-            const long long qv = emitter ? fixed_point(sum * wt[ax], E) : 0;
-            add_fixed(tap + D->delta[dsel[ax]][lev], ch, qv, acc, small, small_off);
+            add_footprint(t, e, k, lev, D->delta[dsel[ax]][lev], ch, emitter ? fixed_point(sum * wt[ax], t.E) : 0);
         }
     });
 }
@@ -383,33 +386,27 @@ __device__ __forceinline__ void emit_level_dirs(bool live, const LevelGeom& geo,
 // place of once per direction: the group loop, the slot-order weights and the
 // clamp key are shared by the three.)
 template <bool ALPHA_ONLY>
-__device__ __forceinline__ void emit_level_axes(bool live, const LevelGeom& geo, float wl, const float gs[4],
-                                                const EmitLane& e, int E, const float wt[3], int sgn,
-                                                const DirTable* D, unsigned long long* __restrict__ acc,
-                                                unsigned long long* small, uint32_t small_off, int lane) {
+__device__ __forceinline__ void emit_level_axes(const Scatter& t, bool live, const LevelGeom& geo, float wl,
+                                                const float gs[4], const EmitLane& e, const float wt[3], int sgn,
+                                                const DirTable* D) {
+    const int lane = t.lane;
     unsigned long long mask = __ballot(live);
     if (mask == 0) return;   // (wave-uniform)
-    float wp[8];
-    emit_weights(geo, wl, e, wp);
+    float ex, ey, ez, wp[8];
+    inner_weights(geo, ex, ey, ez);
+    emit_weights(ex, ey, ez, wl, e, wp);
     float wpart[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) wpart[k] = dpp<kDppXor15>(wp[k + 4]);
-    const uint32_t key = live ? geo.base : 0xffffffffu;
-    const int kcl = (geo.dx == 0 ? 1 : 0) | (geo.dy == 0 ? 2 : 0) | (geo.dz == 0 ? 4 : 0) | (sgn << 3);
     const bool emitter = ALPHA_ONLY ? ((lane & 0x31) == 0) : (lane < 32);
     const int ch = ALPHA_ONLY ? 3 : e.ch;
     while (mask) {
         const int leader = __builtin_ctzll(mask);
-        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key, leader);
-        const int kc = __builtin_amdgcn_readlane(kcl, leader);
-        const bool in = live && key == k && kcl == kc;
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)geo.base, leader);
+        const int sg = __builtin_amdgcn_readlane(sgn, leader);
+        const bool in = live && geo.base == k && sgn == sg;
         const unsigned long long gm = __ballot(in);
         const int lev = __builtin_amdgcn_readlane(geo.level, leader);
-        const uint32_t dx = (uint32_t)__builtin_amdgcn_readlane((int)geo.dx, leader);
-        const uint32_t dy = (uint32_t)__builtin_amdgcn_readlane((int)geo.dy, leader);
-        const uint32_t dz = (uint32_t)__builtin_amdgcn_readlane((int)geo.dz, leader);
-        const uint32_t tap = k + (dx & e.xm) + (dy & e.ym) + (dz & e.zm);
-        const int sg = kc >> 3;
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             float sum;
@@ -421,65 +418,57 @@ __device__ __forceinline__ void emit_level_axes(bool live, const LevelGeom& geo,
                 for (int m = 0; m < 4; ++m) g[m] = in ? gs[m] * wt[ax] : 0.f;
                 sum = bfly32(wp, wpart, g);
             }
-            const long long qv = emitter ? fixed_point(sum, E) : 0;
-            add_fixed(tap + D->delta[2 * ax + ((sg >> ax) & 1)][lev], ch, qv, acc, small, small_off);
+            add_footprint(t, e, k, lev, D->delta[2 * ax + ((sg >> ax) & 1)][lev], ch, emitter ? fixed_point(sum, t.E) : 0);
         }
         mask &= ~gm;
     }
 }
 
-// One level's emission.  Isotropic pyramids: level l's integers carry the
-// scale 2^(E - 3l) (the 1/8 per level of the mip adjoint folded in).
 // Anisotropic pyramids: scale 2^E at every level (their mip adjoint is not a
 // fixed factor); above level 0 the sample read the three directions of its
 // axis signs with weights w_a^2, so each gets the gradient with that weight at
 // its direction's offset: with one butterfly per group when the wave's lanes
 // share their axis (emit_level_dirs), else one per axis in a group keyed by the
 // footprint and the axis's signs (emit_level_axes).
-template <bool ALPHA_ONLY, bool ANISO, bool HOLD>
-__device__ __forceinline__ void emit_dirs(const TraceArgs& a, const DirTable* D, const Cone& c, bool live,
-                                          const LevelGeom& geo, float wl, const float gs[4], const EmitLane& e, int E,
-                                          unsigned long long* __restrict__ acc, unsigned long long* small,
-                                          uint32_t small_off, int lane, Held* held) {
-    if constexpr (!ANISO) {
-        emit_level<ALPHA_ONLY, HOLD>(live, geo, wl, gs, e, E, 3, acc, small, small_off, lane, held);
-    } else {
-        const bool base_level = live && geo.level == 0;
-        emit_level<ALPHA_ONLY>(base_level, geo, wl, gs, e, E, 0, acc, small, small_off, lane);
-        const float W[3] = {c.Wx, c.Wy, c.Wz};
-        const bool up = live && !base_level;
-        const unsigned long long upm = __ballot(up);
-        if (upm == 0) return;
-        const int ld = __builtin_ctzll(upm);
-        const float Wl[3] = {__int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[0]), ld)),
-                             __int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[1]), ld)),
-                             __int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[2]), ld))};
-        const bool same = __float_as_int(W[0]) == __float_as_int(Wl[0]) &&
-                          __float_as_int(W[1]) == __float_as_int(Wl[1]) &&
-                          __float_as_int(W[2]) == __float_as_int(Wl[2]);
-        if (__ballot(up && !same) == 0) {
-            float wt[3];
-            int dsel[3];
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                wt[ax] = Wl[ax] * Wl[ax] * a.inv_scale2;
-                dsel[ax] = 2 * ax + (Wl[ax] < 0.0f ? 1 : 0);
-            }
-            emit_level_dirs<ALPHA_ONLY>(up, geo, wl, gs, e, E, wt, dsel, D, acc, small, small_off, lane);
-            return;
-        }
-        // (a lane of a pixel with no surface has no cone and its W is whatever
-        // the registers held: its axis weights and signs are only read through
-        // the group test, which such a lane never passes)
+template <bool ALPHA_ONLY>
+__device__ __forceinline__ void emit_dirs(const Scatter& t, const TraceArgs& a, const DirTable* D, const Cone& c, bool live,
+                                          const LevelGeom& geo, float wl, const float gs[4], const EmitLane& e) {
+    const bool base_level = live && geo.level == 0;
+    emit_groups<ALPHA_ONLY>(base_level, geo, wl, gs, e, t.lane, [&](uint32_t k, int lev, float sum, bool emitter, int ch) {
+        add_footprint(t, e, k, lev, 0u, ch, emitter ? fixed_point(sum, t.E) : 0);
+    });
+    const float W[3] = {c.Wx, c.Wy, c.Wz};
+    const bool up = live && !base_level;
+    const unsigned long long upm = __ballot(up);
+    if (upm == 0) return;
+    const int ld = __builtin_ctzll(upm);
+    const float Wl[3] = {__int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[0]), ld)),
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[1]), ld)),
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(W[2]), ld))};
+    const bool same = __float_as_int(W[0]) == __float_as_int(Wl[0]) && __float_as_int(W[1]) == __float_as_int(Wl[1]) &&
+                      __float_as_int(W[2]) == __float_as_int(Wl[2]);
+    if (__ballot(up && !same) == 0) {
         float wt[3];
-        int sgn = 0;
+        int dsel[3];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            wt[ax] = W[ax] * W[ax] * a.inv_scale2;
-            sgn |= (W[ax] < 0.0f ? 1 : 0) << ax;
+            wt[ax] = Wl[ax] * Wl[ax] * a.inv_scale2;
+            dsel[ax] = 2 * ax + (Wl[ax] < 0.0f ? 1 : 0);
         }
-        emit_level_axes<ALPHA_ONLY>(up, geo, wl, gs, e, E, wt, sgn, D, acc, small, small_off, lane);
+        emit_level_dirs<ALPHA_ONLY>(t, up, geo, wl, gs, e, wt, dsel, D);
+        return;
     }
+    // (a lane of a pixel with no surface has no cone and its W is whatever
+    // the registers held: its axis weights and signs are only read through
+    // the group test, which such a lane never passes)
+    float wt[3];
+    int sgn = 0;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        wt[ax] = W[ax] * W[ax] * a.inv_scale2;
+        sgn |= (W[ax] < 0.0f ? 1 : 0) << ax;
+    }
+    emit_level_axes<ALPHA_ONLY>(t, up, geo, wl, gs, e, wt, sgn, D);
 }
 
 constexpr int kSmallMax = 704;        // texels of all levels with side <= 8 (8^3 + 3 bricks of 64)
@@ -498,6 +487,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     load_dir_table(a, &D);
     for (int i = threadIdx.x; i < small_n * 4; i += kThreads) s_small[i] = 0ull;
     __syncthreads();
+    if (ctl[1] != 0) return;   // (a bound that is not finite: the gradient is NaN everywhere)
     const int E = ctl[0];
     const int lane = threadIdx.x & 63;
     const int tile = xcd_tile(blockIdx.x, a.n_tiles);
@@ -508,6 +498,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     const bool valid = inb && a.normal[pix].w != 0.0f;
     const int nslots = a.n_diffuse + 2;
     const EmitLane e = emit_lane(lane);
+    const Scatter sc = {acc, s_small, small_off, E, 31 - __builtin_clz(a.n), lane};
     for (int slot = 0; slot < nslots; ++slot) {
         if (!slot_enabled(a, slot)) continue;
         Pass2Lane L;
@@ -526,41 +517,46 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
         const bool occ = slot == a.n_diffuse + 1;
         // Held emissions (isotropic pyramids; the anisotropic ones emit four
         // interleaved direction keys per level and add every group at once).
-        constexpr bool kHold = !ANISO;
         Held held[2];
         held[0].key = held[1].key = kNoKey;
-        held[0].kc = held[1].kc = 0;
-        held[0].dx = held[0].dy = held[0].dz = held[1].dx = held[1].dy = held[1].dz = 0u;
+        held[0].level = held[1].level = 0;
         held[0].qv = held[1].qv = 0;
         for (int k = 0; k < Kw; ++k) {
             const bool live = k < L.K;
-            // lanes past their K only need finite weights for the butterfly
+            // lanes past their K only need finite weights for the sums
             Pass2Step st;
             st.f = 0.f;
             st.g0.wx = st.g0.wy = st.g0.wz = 0.f;
             st.g1.wx = st.g1.wy = st.g1.wz = 0.f;
             if constexpr (ANISO) st.g0.level = st.g1.level = 0;   // (a dead lane's direction-table row)
             if (live) pass2_step<DT, ANISO>(a, T, L, k, st, dir_ptr(D));
-            if (occ) {
-                emit_dirs<true, ANISO, kHold>(a, dir_ptr(D), L.c, live, st.g0, 1.0f - st.f, st.g, e, E, acc,
-                                              s_small, small_off, lane, held);
-                emit_dirs<true, ANISO, kHold>(a, dir_ptr(D), L.c, live && st.f > 0.0f, st.g1, st.f, st.g, e, E,
-                                              acc, s_small, small_off, lane, held);
+            const bool two = live && st.f > 0.0f;
+            // gradient in the lane's slot order (channel bit 1 flipped where cf);
+            // selects on values: an index select would move st to scratch memory
+            const float g0 = st.g[0], g1 = st.g[1], g2 = st.g[2], g3 = st.g[3];
+            const float gs[4] = {e.cf ? g2 : g0, e.cf ? g3 : g1, e.cf ? g0 : g2, e.cf ? g1 : g3};
+            if constexpr (ANISO) {
+                if (occ) {
+                    emit_dirs<true>(sc, a, dir_ptr(D), L.c, live, st.g0, 1.0f - st.f, st.g, e);
+                    emit_dirs<true>(sc, a, dir_ptr(D), L.c, two, st.g1, st.f, st.g, e);
+                } else {
+                    emit_dirs<false>(sc, a, dir_ptr(D), L.c, live, st.g0, 1.0f - st.f, gs, e);
+                    emit_dirs<false>(sc, a, dir_ptr(D), L.c, two, st.g1, st.f, gs, e);
+                }
             } else {
-                // gradient in the lane's slot order (channel bit 1 flipped where cf);
-                // selects on values: an index select would move st to scratch memory
-                const float g0 = st.g[0], g1 = st.g[1], g2 = st.g[2], g3 = st.g[3];
-                const float gs[4] = {e.cf ? g2 : g0, e.cf ? g3 : g1, e.cf ? g0 : g2, e.cf ? g1 : g3};
-                emit_dirs<false, ANISO, kHold>(a, dir_ptr(D), L.c, live, st.g0, 1.0f - st.f, gs, e, E, acc,
-                                               s_small, small_off, lane, held);
-                emit_dirs<false, ANISO, kHold>(a, dir_ptr(D), L.c, live && st.f > 0.0f, st.g1, st.f, gs, e, E,
-                                               acc, s_small, small_off, lane, held);
+                if (occ) {
+                    emit_level<true>(sc, live, st.g0, 1.0f - st.f, st.g, e, held);
+                    emit_level<true>(sc, two, st.g1, st.f, st.g, e, held);
+                } else {
+                    emit_level<false>(sc, live, st.g0, 1.0f - st.f, gs, e, held);
+                    emit_level<false>(sc, two, st.g1, st.f, gs, e, held);
+                }
             }
         }
-        if constexpr (kHold) {
+        if constexpr (!ANISO) {
             // (the occlusion cone's values are all channel 3)
-            flush_held(held[0], e, occ ? 3 : e.ch, acc, s_small, small_off);
-            flush_held(held[1], e, occ ? 3 : e.ch, acc, s_small, small_off);
+            flush_held(sc, held[0], e, occ ? 3 : e.ch);
+            flush_held(sc, held[1], e, occ ? 3 : e.ch);
         }
     }
     __syncthreads();

@@ -87,6 +87,13 @@ __device__ __forceinline__ void acc_colour(df& C, float T, float s) {
     C.lo += p.lo;
 }
 
+// Its reverse: R -= T * s.
+__device__ __forceinline__ void sub_colour(df& R, float T, float s) {
+    df p = two_prod(T, s);
+    R = df_add(R, -p.hi);
+    R.lo -= p.lo;
+}
+
 struct Pass1Out {
     df C[3];
     float A, Tlast, ST, SQ, MC;
@@ -257,11 +264,13 @@ __device__ __forceinline__ void trace_save_pixel(const TraceArgs& a, const Level
     }
 }
 
-// Pass-2 state of one cone of one lane.
+// Pass-2 state of one cone of one lane.  (R in place of C_K and C_k: 6 registers and 9
+// instructions a sample fewer.  With it, the fixed point's two signed words and
+// footprints known by their base texel alone, the scatter pass went 4.95 -> 4.75 ms at
+// 1080p / 256^3, 9.81 -> 9.37 ms anisotropic.)
 struct Pass2Lane {
     Cone c;
-    df C[3];
-    df CK[3];
+    df R[3];      // C_K - C_k: what the samples still to come add
     df t;
     float A, TK;
     float gc[3], ga;
@@ -274,12 +283,11 @@ __device__ __forceinline__ void pass2_init(const TraceArgs& a, const PixelSetup&
     slot_grads(a, slot, g0, g1, L.gc, L.ga);
     const bool zero = L.gc[0] == 0.f && L.gc[1] == 0.f && L.gc[2] == 0.f && L.ga == 0.f;
     L.K = zero ? 0 : min(max(__float_as_int(S.lo.w), 0), a.max_steps);
-    L.CK[0] = {S.hi.x, S.lo.x};
-    L.CK[1] = {S.hi.y, S.lo.y};
-    L.CK[2] = {S.hi.z, S.lo.z};
+    L.R[0] = {S.hi.x, S.lo.x};
+    L.R[1] = {S.hi.y, S.lo.y};
+    L.R[2] = {S.hi.z, S.lo.z};
     L.TK = 1.0f - S.hi.w;
     L.c = cone_for_slot(a, P, slot, cam);
-    for (int i = 0; i < 3; ++i) L.C[i] = {0.f, 0.f};
     L.A = 0.f;
     L.t = {a.t0, 0.0f};
 }
@@ -419,9 +427,9 @@ __device__ __forceinline__ void pass2_step(const TraceArgs& a, const LevelTable&
         s.w = __builtin_fmaf(st.f, s1.w, gg * s.w);
     }
     const float tr = 1.0f - L.A;
-    acc_colour(L.C[0], tr, s.x);
-    acc_colour(L.C[1], tr, s.y);
-    acc_colour(L.C[2], tr, s.z);
+    sub_colour(L.R[0], tr, s.x);
+    sub_colour(L.R[1], tr, s.y);
+    sub_colour(L.R[2], tr, s.z);
     L.A = __builtin_fmaf(tr, s.w, L.A);
     st.g[0] = tr * L.gc[0];
     st.g[1] = tr * L.gc[1];
@@ -432,17 +440,22 @@ __device__ __forceinline__ void pass2_step(const TraceArgs& a, const LevelTable&
         const float tn = 1.0f - L.A;
         float dot = 0.f;
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            float diff = (L.CK[ch].hi - L.C[ch].hi) + (L.CK[ch].lo - L.C[ch].lo);
-            dot = __builtin_fmaf(L.gc[ch], diff, dot);
-        }
+        for (int ch = 0; ch < 3; ++ch) dot = __builtin_fmaf(L.gc[ch], L.R[ch].hi + L.R[ch].lo, dot);
         st.g[3] = -tr * (dot - L.ga * L.TK) * __builtin_amdgcn_rcpf(tn);   // tn >= 2^-24: rcp is 1 ulp
     }
     L.t = df_add(L.t, a.step_factor * d);
 }
 
-// round(v * 2^e) as a 64-bit integer (float32 ops only: the float64 units of
-// gfx950 run at a fraction of the float32 rate).
-__device__ __forceinline__ long long fixed_point(float v, int e) { return (long long)rintf(ldexpf(v, e)); }
+// round(v * 2^e) as a 64-bit integer, |v * 2^e| < 2^62 (float32 ops only: the
+// float64 units of gfx950 run at a fraction of the float32 rate).  Split at
+// the nearest multiple of 2^32, so that both words convert exactly as signed
+// 32-bit integers, with no sign and carry handling.
+__device__ __forceinline__ long long fixed_point(float v, int e) {
+    const float x = rintf(ldexpf(v, e));
+    const float hi = rintf(x * 0x1p-32f);
+    const float lo = fminf(__builtin_fmaf(hi, -0x1p32f, x), 0x1.fffffep30f);   // (2^31 only for a tie: one ulp less)
+    const int l = (int)lo;
+    return (long long)(((unsigned long long)(uint32_t)((int)hi + (l >> 31)) << 32) | (uint32_t)l);
+}
 
 }  // namespace vct
