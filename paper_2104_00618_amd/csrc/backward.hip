@@ -85,6 +85,54 @@ __global__ __launch_bounds__(kThreads, 4) void k_trace_save(TraceArgs a, float4*
     out[2 * pix + 1] = o1;
 }
 
+// The saving forward of small frames (Tile8).  out may be null (the recompute
+// backward's pass 1).
+template <int DT, bool ANISO>
+__global__ __launch_bounds__(64 * kSplitWaves, 4) void k_trace_save_split(TraceArgs a, float4* __restrict__ out,
+                                                                       LaneState* __restrict__ state) {
+    __shared__ LevelTable T;
+    __shared__ DirSlot<ANISO> D;
+    __shared__ float4 s_end[VCT_MAX_DIFFUSE + 2][64];
+    __shared__ int s_next;
+    load_level_table(a, &T);
+    load_dir_table(a, &D);
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    const Tile8 tl = tiles8(a);
+    const int lane = threadIdx.x & 63;
+    int view, y, x;
+    tile8_pixel(tl, xcd_tile(blockIdx.x, tl.n), lane, view, y, x);
+    const bool inb = x < a.w && y < a.h;
+    const size_t pix = inb ? ((size_t)view * a.h + y) * a.w + x : 0;
+    const float4 nr = inb ? a.normal[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const bool valid = nr.w != 0.0f;
+    take_items(&s_next, a.n_diffuse + 2, [&](int i) {
+        const int slot = item_slot(a, i);
+        LaneState st = zero_lane_state();
+        if (valid && slot_enabled(a, slot)) {
+            const PixelSetup P = pixel_setup(a, a.pos_rough[pix], nr);
+            const float3 cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
+            const Pass1Out r = pass1_march<DT, ANISO>(a, T, cone_for_slot(a, P, slot, cam), dir_ptr(D));
+            st = lane_state(r);
+            s_end[slot][lane] = make_float4(r.C[0].hi + r.C[0].lo, r.C[1].hi + r.C[1].lo, r.C[2].hi + r.C[2].lo, r.A);
+        }
+        if (inb) lane_put(a, state, pix, slot, st);
+    });
+    if (!out) return;
+    __syncthreads();
+    if (threadIdx.x < 64 && inb) {
+        float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0;
+        if (valid)
+            for (int slot = 0; slot < a.n_diffuse + 2; ++slot)
+                if (slot_enabled(a, slot)) {
+                    const float4 m = s_end[slot][lane];
+                    add_slot(a, slot, m.x, m.y, m.z, m.w, o0, o1);
+                }
+        out[2 * pix] = o0;
+        out[2 * pix + 1] = o1;
+    }
+}
+
 // Per-workgroup bound sums from saved lane states (same tiles and summation
 // order as pass 1, so the scale exponent is the same).
 __global__ __launch_bounds__(kThreads) void k_bwd_bound(TraceArgs a, const float4* __restrict__ gout,
@@ -479,7 +527,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
                                                         const LaneState* __restrict__ state,
                                                         const int* __restrict__ ctl,
                                                         unsigned long long* __restrict__ acc, uint32_t small_off,
-                                                        int small_n) {
+                                                        int small_n, int split) {
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ unsigned long long s_small[(ANISO ? kSmallMaxAniso : kSmallMax) * 4];
@@ -490,16 +538,27 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     if (ctl[1] != 0) return;   // (a bound that is not finite: the gradient is NaN everywhere)
     const int E = ctl[0];
     const int lane = threadIdx.x & 63;
-    const int tile = xcd_tile(blockIdx.x, a.n_tiles);
-    int view, y, x;
-    tile_pixel(a, tile, threadIdx.x, view, y, x);
+    // one wave marches every cone of an 8x8 quadrant of a 16x16 tile or, on small
+    // frames (Tile8), one cone of an 8x8 tile (four tiles a workgroup, the
+    // specular cones first: the longest)
+    int view, y, x, slot0 = 0, slot1 = a.n_diffuse + 2;
+    if (split) {
+        const Tile8 tl = tiles8(a);
+        const int groups = (tl.n + 3) >> 2, item = (int)blockIdx.x / groups;
+        const int tile = xcd_tile((int)blockIdx.x - item * groups, groups) * 4 + (int)(threadIdx.x >> 6);
+        tile8_pixel(tl, min(tile, tl.n - 1), lane, view, y, x);
+        if (tile >= tl.n) x = a.w;   // (the last group's surplus waves have no pixels)
+        slot0 = item_slot(a, item);
+        slot1 = slot0 + 1;
+    } else {
+        tile_pixel(a, xcd_tile(blockIdx.x, a.n_tiles), threadIdx.x, view, y, x);
+    }
     const bool inb = x < a.w && y < a.h;
     const size_t pix = inb ? ((size_t)view * a.h + y) * a.w + x : 0;
     const bool valid = inb && a.normal[pix].w != 0.0f;
-    const int nslots = a.n_diffuse + 2;
     const EmitLane e = emit_lane(lane);
     const Scatter sc = {acc, s_small, small_off, E, 31 - __builtin_clz(a.n), lane};
-    for (int slot = 0; slot < nslots; ++slot) {
+    for (int slot = slot0; slot < slot1; ++slot) {
         if (!slot_enabled(a, slot)) continue;
         Pass2Lane L;
         L.K = 0;
@@ -734,8 +793,12 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
     hipLaunchKernelGGL(k_fill_zero, dim3(fb), dim3(256), 0, s, reinterpret_cast<uint4*>(acc), n16);
     const float4* g4 = reinterpret_cast<const float4*>(grad_out);
     es.mark(s);
+    const bool split_march = !saved && vct_split_forward(a), split = vct_split_scatter(a);
     if (a.n_tiles > 0) {
-        if (saved)
+        if (split_march)
+            hipLaunchKernelGGL((k_trace_save_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, s, a, nullptr,
+                               state);
+        if (saved || split_march)
             hipLaunchKernelGGL(k_bwd_bound, dim3(a.n_tiles), dim3(kThreads), 0, s, a, g4, state, part);
         else
             hipLaunchKernelGGL((k_bwd_pass1<DT, ANISO>), dim3(a.n_tiles), dim3(kThreads), 0, s, a, g4, state, part);
@@ -756,8 +819,9 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
     if (small_n > (ANISO ? kSmallMaxAniso : kSmallMax)) return hipErrorInvalidValue;
     es.mark(s);
     if (a.n_tiles > 0) {
-        hipLaunchKernelGGL((k_bwd_pass2<DT, ANISO>), dim3(a.n_tiles), dim3(kThreads), 0, s, a, g4, state, ctl, acc,
-                           small_off, small_n);
+        const int blocks = split ? (tiles8(a).n + 3) / 4 * (a.n_diffuse + 2) : a.n_tiles;
+        hipLaunchKernelGGL((k_bwd_pass2<DT, ANISO>), dim3(blocks), dim3(kThreads), 0, s, a, g4, state, ctl, acc,
+                           small_off, small_n, split ? 1 : 0);
     }
     if constexpr (ANISO) {
         AnisoAdj m{};
@@ -842,7 +906,13 @@ hipError_t vct_launch_trace_save(const TraceArgs& a, int dtype, float* out, void
         LaneState* st = reinterpret_cast<LaneState*>(state);
         (void)vct_dispatch_dt(dtype, a.wide != 0, [&](auto dt) {   // (launch errors: hipGetLastError below)
             constexpr int DT = decltype(dt)::value;
-            if (a.aniso)
+            if (vct_split_forward(a)) {
+                const dim3 grid(tiles8(a).n), block(64 * kSplitWaves);
+                if (a.aniso)
+                    hipLaunchKernelGGL((k_trace_save_split<DT, true>), grid, block, 0, s, a, o, st);
+                else
+                    hipLaunchKernelGGL((k_trace_save_split<DT, false>), grid, block, 0, s, a, o, st);
+            } else if (a.aniso)
                 hipLaunchKernelGGL((k_trace_save<DT, true>), dim3(a.n_tiles), dim3(kThreads), 0, s, a, o, st);
             else
                 hipLaunchKernelGGL((k_trace_save<DT, false>), dim3(a.n_tiles), dim3(kThreads), 0, s, a, o, st);

@@ -74,12 +74,6 @@ __device__ __forceinline__ void slot_grads(const TraceArgs& a, int slot, float4 
     }
 }
 
-__device__ __forceinline__ bool slot_enabled(const TraceArgs& a, int slot) {
-    if (slot < a.n_diffuse) return true;
-    if (slot == a.n_diffuse) return a.enable_spec != 0;
-    return a.enable_occ != 0;
-}
-
 // Compensated colour accumulation C += T * s (per channel).
 __device__ __forceinline__ void acc_colour(df& C, float T, float s) {
     df p = two_prod(T, s);

@@ -72,8 +72,18 @@ __device__ __forceinline__ df df_mul(df a, df b) {
     return fast_two_sum(p.hi, lo);
 }
 
+// Sums of products with their FMAs written out.  A cone's axis must have the
+// same bits in every kernel that sets it up (its sample count hangs on them),
+// and which product of a sum the compiler fuses differs from kernel to kernel.
+__device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, float by, float bz) {
+    return __builtin_fmaf(az, bz, __builtin_fmaf(ax, bx, ay * by));
+}
+
+// a b - c d
+__device__ __forceinline__ float diff_products(float a, float b, float c, float d) { return __builtin_fmaf(a, b, -(c * d)); }
+
 __device__ __forceinline__ float3 normalize3(float x, float y, float z) {
-    float r = sqrtf(x * x + y * y + z * z);
+    float r = sqrtf(dot3(x, y, z, x, y, z));
     return make_float3(x / r, y / r, z / r);
 }
 
@@ -323,7 +333,8 @@ __device__ __forceinline__ df to_texel(const TraceArgs& a, float x, int ax) {
 // Unit normal and tangent frame of a cone origin (frame helper axis x if the
 // normal is near +-y, else y).
 __device__ __forceinline__ void set_frame(PixelSetup& P, float4 nr) {
-    float3 n = normalize3(nr.x, nr.y, nr.z);
+    const float len = sqrtf(dot3(nr.y, nr.x, nr.z, nr.y, nr.x, nr.z));
+    const float3 n = make_float3(nr.x / len, nr.y / len, nr.z / len);
     P.nx = n.x;
     P.ny = n.y;
     P.nz = n.z;
@@ -333,14 +344,14 @@ __device__ __forceinline__ void set_frame(PixelSetup& P, float4 nr) {
         ay = 0.f;
     }
     // t = normalize(a x n) with a = (ax, ay, 0)
-    float3 t = normalize3(ay * n.z, -ax * n.z, ax * n.y - ay * n.x);
+    float3 t = normalize3(ay * n.z, -ax * n.z, diff_products(ax, n.y, ay, n.x));
     P.tx = t.x;
     P.ty = t.y;
     P.tz = t.z;
     // b = n x t
-    P.bx = n.y * t.z - n.z * t.y;
-    P.by = n.z * t.x - n.x * t.z;
-    P.bz = n.x * t.y - n.y * t.x;
+    P.bx = diff_products(n.y, t.z, n.z, t.y);
+    P.by = diff_products(n.z, t.x, n.x, t.z);
+    P.bz = diff_products(n.x, t.y, n.y, t.x);
 }
 
 // Cone origin offset from texel-space point X along the unit normal:
@@ -376,19 +387,24 @@ __device__ __forceinline__ Cone make_cone(const TraceArgs& a, const PixelSetup& 
     return c;
 }
 
+// Unit reflection of the unit vector v about the pixel's normal.
+__device__ __forceinline__ float3 reflect3(float3 v, const PixelSetup& P) {
+    const float vn2 = -2.f * dot3(v.x, v.y, v.z, P.nx, P.ny, P.nz);
+    return normalize3(__builtin_fmaf(vn2, P.nx, v.x), __builtin_fmaf(vn2, P.ny, v.y), __builtin_fmaf(vn2, P.nz, v.z));
+}
+
 // Axis of cone slot `slot` of a pixel (0..u-1 diffuse, u specular, u+1 occlusion);
 // sets aperture and t_max.
 __device__ __forceinline__ Cone cone_for_slot(const TraceArgs& a, const PixelSetup& P, int slot, float3 cam) {
     if (slot < a.n_diffuse) {
         float dx = a.dir[slot][0], dy = a.dir[slot][1], dz = a.dir[slot][2];
-        float3 w = normalize3(P.tx * dx + P.bx * dy + P.nx * dz, P.ty * dx + P.by * dy + P.ny * dz,
-                              P.tz * dx + P.bz * dy + P.nz * dz);
+        float3 w = normalize3(dot3(P.tx, P.bx, P.nx, dx, dy, dz), dot3(P.ty, P.by, P.ny, dx, dy, dz),
+                              dot3(P.tz, P.bz, P.nz, dx, dy, dz));
         return make_cone(a, P, w, a.diffuse_aperture, a.max_dist);
     }
     if (slot == a.n_diffuse) {
         float3 v = normalize3(P.px - cam.x, P.py - cam.y, P.pz - cam.z);
-        float vn = v.x * P.nx + v.y * P.ny + v.z * P.nz;
-        float3 r = normalize3(v.x - 2.f * vn * P.nx, v.y - 2.f * vn * P.ny, v.z - 2.f * vn * P.nz);
+        float3 r = reflect3(v, P);
         return make_cone(a, P, r, P.rough * a.spec_aperture_scale, a.max_dist);
     }
     // occlusion: toward the light, in texel units
@@ -398,7 +414,7 @@ __device__ __forceinline__ Cone cone_for_slot(const TraceArgs& a, const PixelSet
     float dx = (Lx.hi - P.Ox.hi) + (Lx.lo - P.Ox.lo);
     float dy = (Ly.hi - P.Oy.hi) + (Ly.lo - P.Oy.lo);
     float dz = (Lz.hi - P.Oz.hi) + (Lz.lo - P.Oz.lo);
-    float len = sqrtf(dx * dx + dy * dy + dz * dz);
+    float len = sqrtf(dot3(dx, dy, dz, dx, dy, dz));
     float dist = len / a.scale_hi;
     float3 w = len > 0.f ? make_float3(dx / len, dy / len, dz / len) : make_float3(0.f, 0.f, 0.f);
     return make_cone(a, P, w, a.occ_aperture, fminf(a.max_dist, dist));
@@ -493,6 +509,31 @@ __device__ __forceinline__ MarchResult march(const TraceArgs& a, const LevelTabl
     return m;
 }
 
+__device__ __forceinline__ bool slot_enabled(const TraceArgs& a, int slot) {
+    if (slot < a.n_diffuse) return true;
+    if (slot == a.n_diffuse) return a.enable_spec != 0;
+    return a.enable_occ != 0;
+}
+
+// Adds the end state (C, A) of cone `slot` to the 8-float epilogue (D.rgb,
+// D.a, S.rgb, O) of its pixel; called for the slots in order.
+__device__ __forceinline__ void add_slot(const TraceArgs& a, int slot, float r, float g, float b, float al, float4& o0,
+                                         float4& o1) {
+    if (slot < a.n_diffuse) {
+        const float wq = a.weight[slot];
+        o0.x = __builtin_fmaf(wq, r, o0.x);
+        o0.y = __builtin_fmaf(wq, g, o0.y);
+        o0.z = __builtin_fmaf(wq, b, o0.z);
+        o0.w = __builtin_fmaf(wq, al, o0.w);
+    } else if (slot == a.n_diffuse) {
+        o1.x = r;
+        o1.y = g;
+        o1.z = b;
+    } else {
+        o1.w = al;
+    }
+}
+
 // All cones of one pixel (slots 0..u-1 diffuse, specular, occlusion); the
 // 8-float epilogue (D.rgb, D.a, S.rgb, O) goes to o0, o1, the sample count to
 // ksum and the count of two-level samples to k2sum.
@@ -557,5 +598,55 @@ __device__ __forceinline__ void tile_pixel(const TraceArgs& a, int tile, int tid
     x = tx * 16 + (wv & 1) * 8 + (lane & 7);
     y = ty * 16 + (wv >> 1) * 8 + (lane >> 3);
 }
+
+// ---------------------------------------------------------------------------
+// Small frames: cones spread over waves.
+//
+// One lane for each pixel leaves the chip short of waves on a small frame (256 x
+// 256 is one wave for each SIMD), and its time is the chain of all the cones of a
+// pixel.  There a workgroup of kSplitWaves waves takes one 8x8-pixel tile, and its
+// waves take the tile's cones from a counter, the specular one first: its
+// narrow cone takes about as many samples as all the others together, so two
+// waves halve the chain and more than a few find nothing left to do.  The end
+// states meet in LDS and one wave adds them in slot order, as for a large frame.
+// ---------------------------------------------------------------------------
+constexpr int kSplitWaves = 4;
+
+struct Tile8 {
+    int32_t x, y, n;   // tiles per row, rows of tiles per view, tiles of all views
+};
+
+__host__ __device__ inline Tile8 tiles8(const TraceArgs& a) {
+    Tile8 t;
+    t.x = (a.w + 7) >> 3;
+    t.y = (a.h + 7) >> 3;
+    t.n = t.x * t.y * a.b;
+    return t;
+}
+
+__device__ __forceinline__ void tile8_pixel(const Tile8& t, int tile, int lane, int& view, int& y, int& x) {
+    const int tpv = t.x * t.y;
+    view = tile / tpv;
+    const int r = tile - view * tpv;
+    const int ty = r / t.x;
+    x = (r - ty * t.x) * 8 + (lane & 7);
+    y = ty * 8 + (lane >> 3);
+}
+
+// Calls f(i) for the items i = 0..n-1 of a workgroup, each in one of its waves
+// (i is wave-uniform; *next starts at 0 and is shared by the workgroup).
+template <typename F>
+__device__ __forceinline__ void take_items(int* next, int n, F&& f) {
+    for (;;) {
+        int i = 0;
+        if ((threadIdx.x & 63) == 0) i = atomicAdd(next, 1);
+        i = __builtin_amdgcn_readlane(i, 0);
+        if (i >= n) break;
+        f(i);
+    }
+}
+
+// Item i's cone slot: specular, occlusion, then the diffuse ones.
+__device__ __forceinline__ int item_slot(const TraceArgs& a, int i) { return i < 2 ? a.n_diffuse + i : i - 2; }
 
 }  // namespace vct

@@ -52,12 +52,80 @@ __global__ __launch_bounds__(256) void k_shade(TraceArgs a, ShadeArgs s, float4*
     }
 }
 
+// The shading of small frames (Tile8 in march.h): items are the specular cone,
+// the lights' occlusion cones, then the diffuse cones.
+template <int DT, bool ANISO>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_shade_split(TraceArgs a, ShadeArgs s, float4* __restrict__ out) {
+    __shared__ LevelTable T;
+    __shared__ DirSlot<ANISO> D;
+    __shared__ float s_col[VCT_MAX_DIFFUSE + 1][3][64];   // specular, diffuse
+    __shared__ float s_occ[VCT_MAX_LIGHTS][64];
+    __shared__ int s_next;
+    load_level_table(a, &T);
+    load_dir_table(a, &D);
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    const Tile8 tl = tiles8(a);
+    const int lane = threadIdx.x & 63;
+    int view, y, x;
+    tile8_pixel(tl, xcd_tile(blockIdx.x, tl.n), lane, view, y, x);
+    const bool inb = x < a.w && y < a.h;
+    const size_t pix = inb ? ((size_t)view * a.h + y) * a.w + x : 0;
+    const float4 nr = inb ? a.normal[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const bool valid = nr.w != 0.0f;
+    PixelSetup P;
+    float3 cam = make_float3(0.f, 0.f, 0.f);
+    if (valid) {
+        P = pixel_setup(a, a.pos_rough[pix], nr);
+        cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
+    }
+    take_items(&s_next, 1 + s.n_lights + a.n_diffuse, [&](int i) {
+        if (!valid) return;
+        unsigned int n = 0;
+        if (i >= 1 && i <= s.n_lights) {
+            s_occ[i - 1][lane] = shade_occlusion<DT, ANISO>(a, T, dir_ptr(D), s, P, i - 1, n);
+            return;
+        }
+        float3 c;
+        if (i == 0) {
+            const MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, cone_for_slot(a, P, a.n_diffuse, cam), dir_ptr(D));
+            c = make_float3(m.r, m.g, m.b);
+        } else {
+            c = shade_diffuse<DT, ANISO>(a, T, dir_ptr(D), s, P, cam, i - 1 - s.n_lights, n);
+        }
+        const int at = i == 0 ? 0 : i - s.n_lights;
+        s_col[at][0][lane] = c.x;
+        s_col[at][1][lane] = c.y;
+        s_col[at][2][lane] = c.z;
+    });
+    __syncthreads();
+    if (threadIdx.x < 64 && inb) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (valid) {
+            float3 d = make_float3(0.f, 0.f, 0.f);
+            for (int q = 0; q < a.n_diffuse; ++q) {
+                const float wq = a.weight[q];
+                d.x = __builtin_fmaf(wq, s_col[1 + q][0][lane], d.x);
+                d.y = __builtin_fmaf(wq, s_col[1 + q][1][lane], d.y);
+                d.z = __builtin_fmaf(wq, s_col[1 + q][2][lane], d.z);
+            }
+            v = shade_combine(s, P, cam, s.material[pix], d,
+                              make_float3(s_col[0][0][lane], s_col[0][1][lane], s_col[0][2][lane]),
+                              [&](int l) { return s_occ[l][lane]; });
+        }
+        out[pix] = v;
+    }
+}
+
 __global__ void k_zero_count(unsigned long long* p) { *p = 0ull; }
 
 template <int DT, bool ANISO>
 void launch_shade(const TraceArgs& a, const ShadeArgs& s, float* out, unsigned long long* count, hipStream_t st) {
     if (count)
         hipLaunchKernelGGL((k_shade<DT, ANISO, true>), dim3(a.n_tiles), dim3(256), 0, st, a, s, nullptr, count);
+    else if (vct_split_forward(a))
+        hipLaunchKernelGGL((k_shade_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, st, a, s,
+                           reinterpret_cast<float4*>(out));
     else
         hipLaunchKernelGGL((k_shade<DT, ANISO, false>), dim3(a.n_tiles), dim3(256), 0, st, a, s,
                            reinterpret_cast<float4*>(out), nullptr);

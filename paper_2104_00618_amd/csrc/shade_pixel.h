@@ -67,61 +67,50 @@ __device__ __forceinline__ Cone light_cone(const TraceArgs& a, const PixelSetup&
     const float dx = (L[0][0] - P.Ox.hi) + (L[0][1] - P.Ox.lo);
     const float dy = (L[1][0] - P.Oy.hi) + (L[1][1] - P.Oy.lo);
     const float dz = (L[2][0] - P.Oz.hi) + (L[2][1] - P.Oz.lo);
-    const float len = sqrtf(dx * dx + dy * dy + dz * dz);
+    const float len = sqrtf(dot3(dx, dy, dz, dx, dy, dz));
     const float dist = len / a.scale_hi;
     const float3 w = len > 0.f ? make_float3(dx / len, dy / len, dz / len) : make_float3(0.f, 0.f, 0.f);
     return make_cone(a, P, w, a.occ_aperture, fminf(a.max_dist, dist));
 }
 
-// (L.rgb, o_min) of one valid pixel; the samples of all its cones are added to n.
+// Indirect light of diffuse cone q, and the occlusion alpha of light l; the
+// samples taken are added to n.
 template <int DT, bool ANISO>
-__device__ __forceinline__ float4 shade_pixel(const TraceArgs& a, const LevelTable& T, const DirTable* dirs,
-                                              const ShadeArgs& s, int view, size_t pix, float4 nr, unsigned int& n) {
-    const float4 pr = a.pos_rough[pix];
-    const float4 mat = s.material[pix];
-    const PixelSetup P = pixel_setup(a, pr, nr);
-    const float3 cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
+__device__ __forceinline__ float3 shade_diffuse(const TraceArgs& a, const LevelTable& T, const DirTable* dirs,
+                                                const ShadeArgs& s, const PixelSetup& P, float3 cam, int q,
+                                                unsigned int& n) {
+    const Cone c = cone_for_slot(a, P, q, cam);
+    if (s.first_hit) return march_first_hit<DT, ANISO>(a, T, dirs, c, s.first_hit_alpha, n);
+    const MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, c, dirs);
+    n += (unsigned int)m.k;
+    return make_float3(m.r, m.g, m.b);
+}
 
-    // indirect diffuse
-    float3 D = make_float3(0.f, 0.f, 0.f);
-    for (int q = 0; q < a.n_diffuse; ++q) {
-        const Cone c = cone_for_slot(a, P, q, cam);
-        float3 col;
-        if (s.first_hit) {
-            col = march_first_hit<DT, ANISO>(a, T, dirs, c, s.first_hit_alpha, n);
-        } else {
-            const MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, c, dirs);
-            col = make_float3(m.r, m.g, m.b);
-            n += (unsigned int)m.k;
-        }
-        const float wq = a.weight[q];
-        D.x = __builtin_fmaf(wq, col.x, D.x);
-        D.y = __builtin_fmaf(wq, col.y, D.y);
-        D.z = __builtin_fmaf(wq, col.z, D.z);
-    }
-    // indirect specular: one trace along the reflection axis
-    const MarchResult ms = march<DT, ANISO, kShareFootprint<DT>>(a, T, cone_for_slot(a, P, a.n_diffuse, cam), dirs);
-    n += (unsigned int)ms.k;
+template <int DT, bool ANISO>
+__device__ __forceinline__ float shade_occlusion(const TraceArgs& a, const LevelTable& T, const DirTable* dirs,
+                                                 const ShadeArgs& s, const PixelSetup& P, int l, unsigned int& n) {
+    const Cone co = light_cone(a, P, s.light_tex[l]);
+    if (s.falloff) return march_falloff<DT, ANISO>(a, T, dirs, co, s.shadow_strength, n);
+    const MarchResult mo = march<DT, ANISO, kShareFootprint<DT>>(a, T, co, dirs);
+    n += (unsigned int)mo.k;
+    return mo.a;
+}
+
+// (L.rgb, o_min) of a pixel from its indirect diffuse light D, its specular
+// cone's colour S and occlusion(l), the occlusion alpha of light l.
+template <typename F>
+__device__ __forceinline__ float4 shade_combine(const ShadeArgs& s, const PixelSetup& P, float3 cam, float4 mat, float3 D,
+                                                float3 S, F&& occlusion) {
     // unit reflection axis (as in the specular cone) and view direction
     const float3 v = normalize3(P.px - cam.x, P.py - cam.y, P.pz - cam.z);
-    const float vn = v.x * P.nx + v.y * P.ny + v.z * P.nz;
-    const float3 r = normalize3(v.x - 2.f * vn * P.nx, v.y - 2.f * vn * P.ny, v.z - 2.f * vn * P.nz);
+    const float3 r = reflect3(v, P);
     const float3 wv = make_float3(-v.x, -v.y, -v.z);
     const float shin = mat.w;
 
     float omin = 1.0f, fsum = 0.0f;
     float3 direct = make_float3(0.f, 0.f, 0.f);
     for (int l = 0; l < s.n_lights; ++l) {
-        const Cone co = light_cone(a, P, s.light_tex[l]);
-        float A;
-        if (s.falloff) {
-            A = march_falloff<DT, ANISO>(a, T, dirs, co, s.shadow_strength, n);
-        } else {
-            const MarchResult mo = march<DT, ANISO, kShareFootprint<DT>>(a, T, co, dirs);
-            A = mo.a;
-            n += (unsigned int)mo.k;
-        }
-        const float V = 1.0f - A;
+        const float V = 1.0f - occlusion(l);
         omin = fminf(omin, V);
         const float3 L = normalize3(s.light_pos[l][0] - P.px, s.light_pos[l][1] - P.py, s.light_pos[l][2] - P.pz);
         const float ndl = P.nx * L.x + P.ny * L.y + P.nz * L.z;
@@ -141,9 +130,32 @@ __device__ __forceinline__ float4 shade_pixel(const TraceArgs& a, const LevelTab
         }
     }
     if (!s.brdf) fsum = 1.0f;
-    return make_float4(__builtin_fmaf(omin, D.x, __builtin_fmaf(fsum, ms.r, direct.x)),
-                       __builtin_fmaf(omin, D.y, __builtin_fmaf(fsum, ms.g, direct.y)),
-                       __builtin_fmaf(omin, D.z, __builtin_fmaf(fsum, ms.b, direct.z)), omin);
+    return make_float4(__builtin_fmaf(omin, D.x, __builtin_fmaf(fsum, S.x, direct.x)),
+                       __builtin_fmaf(omin, D.y, __builtin_fmaf(fsum, S.y, direct.y)),
+                       __builtin_fmaf(omin, D.z, __builtin_fmaf(fsum, S.z, direct.z)), omin);
+}
+
+// The same of one valid pixel with its cones marched one after another; the
+// samples of all its cones are added to n.
+template <int DT, bool ANISO>
+__device__ __forceinline__ float4 shade_pixel(const TraceArgs& a, const LevelTable& T, const DirTable* dirs,
+                                              const ShadeArgs& s, int view, size_t pix, float4 nr, unsigned int& n) {
+    const float4 mat = s.material[pix];
+    const PixelSetup P = pixel_setup(a, a.pos_rough[pix], nr);
+    const float3 cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
+    float3 D = make_float3(0.f, 0.f, 0.f);
+    for (int q = 0; q < a.n_diffuse; ++q) {
+        const float3 col = shade_diffuse<DT, ANISO>(a, T, dirs, s, P, cam, q, n);
+        const float wq = a.weight[q];
+        D.x = __builtin_fmaf(wq, col.x, D.x);
+        D.y = __builtin_fmaf(wq, col.y, D.y);
+        D.z = __builtin_fmaf(wq, col.z, D.z);
+    }
+    // indirect specular: one trace along the reflection axis
+    const MarchResult ms = march<DT, ANISO, kShareFootprint<DT>>(a, T, cone_for_slot(a, P, a.n_diffuse, cam), dirs);
+    n += (unsigned int)ms.k;
+    return shade_combine(s, P, cam, mat, D, make_float3(ms.r, ms.g, ms.b),
+                         [&](int l) { return shade_occlusion<DT, ANISO>(a, T, dirs, s, P, l, n); });
 }
 
 }  // namespace vct

@@ -48,6 +48,51 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a, float4* __restrict__
     }
 }
 
+// The forward of small frames (Tile8).
+template <int DT, bool ANISO>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_trace_split(TraceArgs a, float4* __restrict__ out) {
+    __shared__ LevelTable T;
+    __shared__ DirSlot<ANISO> D;
+    __shared__ float4 s_end[VCT_MAX_DIFFUSE + 2][64];
+    __shared__ int s_next;
+    load_level_table(a, &T);
+    load_dir_table(a, &D);
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    const Tile8 tl = tiles8(a);
+    const int lane = threadIdx.x & 63;
+    int view, y, x;
+    tile8_pixel(tl, xcd_tile(blockIdx.x, tl.n), lane, view, y, x);
+    const bool inb = x < a.w && y < a.h;
+    const size_t pix = inb ? ((size_t)view * a.h + y) * a.w + x : 0;
+    const float4 nr = inb ? a.normal[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const bool valid = nr.w != 0.0f;
+    PixelSetup P;
+    float3 cam = make_float3(0.f, 0.f, 0.f);
+    if (valid) {
+        P = pixel_setup(a, a.pos_rough[pix], nr);
+        cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
+    }
+    take_items(&s_next, a.n_diffuse + 2, [&](int i) {
+        const int slot = item_slot(a, i);
+        if (!valid || !slot_enabled(a, slot)) return;
+        const MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, cone_for_slot(a, P, slot, cam), dir_ptr(D));
+        s_end[slot][lane] = make_float4(m.r, m.g, m.b, m.a);
+    });
+    __syncthreads();
+    if (threadIdx.x < 64 && inb) {
+        float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0;
+        if (valid)
+            for (int slot = 0; slot < a.n_diffuse + 2; ++slot)
+                if (slot_enabled(a, slot)) {
+                    const float4 m = s_end[slot][lane];
+                    add_slot(a, slot, m.x, m.y, m.z, m.w, o0, o1);
+                }
+        out[2 * pix] = o0;
+        out[2 * pix + 1] = o1;
+    }
+}
+
 __global__ void k_zero_u64(unsigned long long* p, int n) {
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
@@ -65,8 +110,12 @@ hipError_t run_trace(const TraceArgs& a, float* out, unsigned long long* count, 
         }
     } else if (a.n_tiles > 0) {
         es.mark(s);
-        hipLaunchKernelGGL((k_trace<DT, false, ANISO>), grid, block, 0, s, a, reinterpret_cast<float4*>(out),
-                           nullptr, 0);
+        if (vct_split_forward(a))
+            hipLaunchKernelGGL((k_trace_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, s, a,
+                               reinterpret_cast<float4*>(out));
+        else
+            hipLaunchKernelGGL((k_trace<DT, false, ANISO>), grid, block, 0, s, a, reinterpret_cast<float4*>(out),
+                               nullptr, 0);
     }
     es.mark(s);
     return hipGetLastError();

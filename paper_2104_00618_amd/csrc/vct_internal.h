@@ -140,6 +140,17 @@ struct TraceArgs {
     int32_t max_steps;             // hard bound on samples per cone
 };
 
+// Frames whose cones are spread over waves of their own (Tile8 in march.h), by
+// their 16x16-pixel tiles.  The forward kernels join a tile's cones at the end, so
+// they gain while one wave per 64 pixels leaves SIMDs short of waves: at 64^3 /
+// 256 x 256 (256 tiles) trace 102 -> 63 us, saving forward 118 -> 69, shading 90 -> 60;
+// even at 512 x 512 (1024), and 633 -> 719 us for the trace at 1280 x 720 (3600).
+// The scatter pass has nothing to join, and its longer chains gain up to larger
+// frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1951 -> 1864 at 1280 x 720,
+// 4594 -> 4637 at 1920 x 1080 (8160).
+static inline bool vct_split_forward(const TraceArgs& a) { return a.n_tiles <= 768; }
+static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= 4096; }
+
 // Calls f(std::integral_constant<int, DT>) with the kernel template argument
 // of a pyramid: its storage type, plus VCT_WIDE when it needs 64-bit fetches.
 template <typename F>
