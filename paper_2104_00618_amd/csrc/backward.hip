@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void k_trace_save_split(TraceA
         if (valid && slot_enabled(a, slot)) {
             const PixelSetup P = pixel_setup(a, a.pos_rough[pix], nr);
             const float3 cam = make_float3(a.cam_pos[3 * view], a.cam_pos[3 * view + 1], a.cam_pos[3 * view + 2]);
-            const Pass1Out r = pass1_march<DT, ANISO>(a, T, cone_for_slot(a, P, slot, cam), dir_ptr(D));
+            const Pass1Out r = pass1_march<DT, ANISO>(a, T, cone_for_slot<true>(a, P, slot, cam), dir_ptr(D));
             st = lane_state(r);
             s_end[slot][lane] = make_float4(r.C[0].hi + r.C[0].lo, r.C[1].hi + r.C[1].lo, r.C[2].hi + r.C[2].lo, r.A);
         }

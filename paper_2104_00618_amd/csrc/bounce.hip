@@ -185,7 +185,7 @@ __global__ __launch_bounds__(1024) void k_gather(TraceArgs a, BounceArgs b) {
             live = nr.x * nr.x + nr.y * nr.y + nr.z * nr.z >= kMinNormal2;
             if (live) {
                 PixelSetup P;
-                set_frame(P, nr);
+                set_frame<false>(P, nr);
                 // the voxel centre (i + 1/2 in texel units) is exact in float
                 const float x = (float)(v & mask), y = (float)((v >> b.lg) & mask), z = (float)(v >> (2 * b.lg));
                 set_origin(a, P, df{x + 0.5f, 0.0f}, df{y + 0.5f, 0.0f}, df{z + 0.5f, 0.0f});

@@ -196,7 +196,7 @@ __device__ __forceinline__ float pass1_pixel(const TraceArgs& a, const LevelTabl
     for (int slot = 0; slot < nslots; ++slot) {
         LaneState out = zero_lane_state();
         if (slot_enabled(a, slot)) {
-            Cone c = cone_for_slot(a, P, slot, cam);
+            Cone c = cone_for_slot<true>(a, P, slot, cam);
             out = lane_state(pass1_march<DT, ANISO>(a, T, c, D));
             bound += lane_bound(a, slot, out.cf, g0, g1);
         }
@@ -236,7 +236,7 @@ __device__ __forceinline__ void trace_save_pixel(const TraceArgs& a, const Level
     for (int slot = 0; slot < nslots; ++slot) {
         LaneState out = zero_lane_state();
         if (slot_enabled(a, slot)) {
-            Cone c = cone_for_slot(a, P, slot, cam);
+            Cone c = cone_for_slot<true>(a, P, slot, cam);
             Pass1Out r = pass1_march<DT, ANISO>(a, T, c, D);
             out = lane_state(r);
             const float cr = r.C[0].hi + r.C[0].lo, cg = r.C[1].hi + r.C[1].lo, cb = r.C[2].hi + r.C[2].lo;

@@ -75,15 +75,18 @@ __device__ __forceinline__ df df_mul(df a, df b) {
 // Sums of products with their FMAs written out.  A cone's axis must have the
 // same bits in every kernel that sets it up (its sample count hangs on them),
 // and which product of a sum the compiler fuses differs from kernel to kernel.
+// (X_FIRST: the product a.x b.x is the one rounded by itself, else a.y b.y.)
+template <bool X_FIRST = false>
 __device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, float by, float bz) {
-    return __builtin_fmaf(az, bz, __builtin_fmaf(ax, bx, ay * by));
+    return __builtin_fmaf(az, bz, X_FIRST ? __builtin_fmaf(ay, by, ax * bx) : __builtin_fmaf(ax, bx, ay * by));
 }
 
 // a b - c d
 __device__ __forceinline__ float diff_products(float a, float b, float c, float d) { return __builtin_fmaf(a, b, -(c * d)); }
 
+template <bool X_FIRST = false>
 __device__ __forceinline__ float3 normalize3(float x, float y, float z) {
-    float r = sqrtf(dot3(x, y, z, x, y, z));
+    float r = sqrtf(dot3<X_FIRST>(x, y, z, x, y, z));
     return make_float3(x / r, y / r, z / r);
 }
 
@@ -332,9 +335,9 @@ __device__ __forceinline__ df to_texel(const TraceArgs& a, float x, int ax) {
 
 // Unit normal and tangent frame of a cone origin (frame helper axis x if the
 // normal is near +-y, else y).
+template <bool X_FIRST = true>
 __device__ __forceinline__ void set_frame(PixelSetup& P, float4 nr) {
-    const float len = sqrtf(dot3(nr.y, nr.x, nr.z, nr.y, nr.x, nr.z));
-    const float3 n = make_float3(nr.x / len, nr.y / len, nr.z / len);
+    const float3 n = normalize3<X_FIRST>(nr.x, nr.y, nr.z);
     P.nx = n.x;
     P.ny = n.y;
     P.nz = n.z;
@@ -394,7 +397,12 @@ __device__ __forceinline__ float3 reflect3(float3 v, const PixelSetup& P) {
 }
 
 // Axis of cone slot `slot` of a pixel (0..u-1 diffuse, u specular, u+1 occlusion);
-// sets aperture and t_max.
+// sets aperture and t_max.  (VIEW_X_FIRST: rounding of the view vector's length in
+// the forward that keeps lane states, pass 1 of the backward with it.  The re-march and
+// the plain trace round it the other way round, so specular axes off the coordinate
+// axes can differ in their last bit, which a saturating cone's gradient shows; both
+// roundings are kept as they were, so that results are.)
+template <bool VIEW_X_FIRST = false>
 __device__ __forceinline__ Cone cone_for_slot(const TraceArgs& a, const PixelSetup& P, int slot, float3 cam) {
     if (slot < a.n_diffuse) {
         float dx = a.dir[slot][0], dy = a.dir[slot][1], dz = a.dir[slot][2];
@@ -403,7 +411,7 @@ __device__ __forceinline__ Cone cone_for_slot(const TraceArgs& a, const PixelSet
         return make_cone(a, P, w, a.diffuse_aperture, a.max_dist);
     }
     if (slot == a.n_diffuse) {
-        float3 v = normalize3(P.px - cam.x, P.py - cam.y, P.pz - cam.z);
+        float3 v = normalize3<VIEW_X_FIRST>(P.px - cam.x, P.py - cam.y, P.pz - cam.z);
         float3 r = reflect3(v, P);
         return make_cone(a, P, r, P.rough * a.spec_aperture_scale, a.max_dist);
     }
