@@ -519,6 +519,27 @@ __device__ __forceinline__ void emit_dirs(const Scatter& t, const TraceArgs& a, 
     emit_level_axes<ALPHA_ONLY>(t, up, geo, wl, gs, e, wt, sgn, D);
 }
 
+// The split scatter pass on the smallest frames: with fewer waves than the chip
+// holds (four for each SIMD, 4096), the time is the chain of one cone's samples, nine
+// tenths of it their groups.  There several waves march the same cone, and each
+// emits every n-th pair of its samples (pairs, since neighbours often share a
+// footprint and are then held together): same groups, same sums, same accumulator.
+// The specular cone takes about twice the others' samples, so it gets more parts.  Past
+// 640 tiles of eight cones the repeated marches cost what the shorter chains give.
+// One part / as here: 16^3, 2 x 32 x 32 (32 tiles) 193 -> 59 us; 64^3, 96 x 96 (144)
+// 371 -> 147, 128 x 128 320 -> 179, 192 x 192 (576) 274 -> 205; 256 x 256 (1024) would
+// go 266 -> 261, and 529 -> 563 with an anisotropic pyramid.
+constexpr int kPartLog = 1;
+struct SplitPlan {
+    int32_t spec, others;   // waves for each specular cone and for each other cone (powers of two); 0: no split
+};
+SplitPlan split_plan(const TraceArgs& a) {
+    const int64_t waves = (int64_t)tiles8(a).n * (a.n_diffuse + 2);
+    const int64_t r = 20480 / (waves > 0 ? waves : 1);
+    if (r < 4) return {1, 1};
+    return r >= 16 ? SplitPlan{16, 4} : r >= 8 ? SplitPlan{8, 4} : SplitPlan{4, 2};
+}
+
 constexpr int kSmallMax = 704;        // texels of all levels with side <= 8 (8^3 + 3 bricks of 64)
 constexpr int kSmallMaxAniso = 1152;  // anisotropic: levels with side <= 4 of six directions (6 x 3 bricks)
 
@@ -527,7 +548,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
                                                         const LaneState* __restrict__ state,
                                                         const int* __restrict__ ctl,
                                                         unsigned long long* __restrict__ acc, uint32_t small_off,
-                                                        int small_n, int split) {
+                                                        int small_n, SplitPlan split) {
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ unsigned long long s_small[(ANISO ? kSmallMaxAniso : kSmallMax) * 4];
@@ -540,15 +561,19 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     const int lane = threadIdx.x & 63;
     // one wave marches every cone of an 8x8 quadrant of a 16x16 tile or, on small
     // frames (Tile8), one cone of an 8x8 tile (four tiles a workgroup, the
-    // specular cones first: the longest)
-    int view, y, x, slot0 = 0, slot1 = a.n_diffuse + 2;
-    if (split) {
+    // specular cones first: the longest), of which it emits one part's samples
+    int view, y, x, slot0 = 0, slot1 = a.n_diffuse + 2, part = 0, part_mask = 0;
+    if (split.spec) {
         const Tile8 tl = tiles8(a);
-        const int groups = (tl.n + 3) >> 2, item = (int)blockIdx.x / groups;
+        const int groups = (tl.n + 3) >> 2;
+        int item = (int)blockIdx.x / groups;
         const int tile = xcd_tile((int)blockIdx.x - item * groups, groups) * 4 + (int)(threadIdx.x >> 6);
         tile8_pixel(tl, min(tile, tl.n - 1), lane, view, y, x);
         if (tile >= tl.n) x = a.w;   // (the last group's surplus waves have no pixels)
-        slot0 = item_slot(a, item);
+        part_mask = (item < split.spec ? split.spec : split.others) - 1;
+        if (item >= split.spec) item += split.others - split.spec;
+        part = item & part_mask;
+        slot0 = item_slot(a, item / (part_mask + 1));
         slot1 = slot0 + 1;
     } else {
         tile_pixel(a, xcd_tile(blockIdx.x, a.n_tiles), threadIdx.x, view, y, x);
@@ -589,6 +614,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
             st.g1.wx = st.g1.wy = st.g1.wz = 0.f;
             if constexpr (ANISO) st.g0.level = st.g1.level = 0;   // (a dead lane's direction-table row)
             if (live) pass2_step<DT, ANISO>(a, T, L, k, st, dir_ptr(D));
+            if (((k >> kPartLog) & part_mask) != part) continue;   // (another wave emits this sample)
             const bool two = live && st.f > 0.0f;
             // gradient in the lane's slot order (channel bit 1 flipped where cf);
             // selects on values: an index select would move st to scratch memory
@@ -819,9 +845,14 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
     if (small_n > (ANISO ? kSmallMaxAniso : kSmallMax)) return hipErrorInvalidValue;
     es.mark(s);
     if (a.n_tiles > 0) {
-        const int blocks = split ? (tiles8(a).n + 3) / 4 * (a.n_diffuse + 2) : a.n_tiles;
+        SplitPlan sp = {0, 0};
+        int blocks = a.n_tiles;
+        if (split) {
+            sp = split_plan(a);
+            blocks = (tiles8(a).n + 3) / 4 * (sp.spec + sp.others * (a.n_diffuse + 1));
+        }
         hipLaunchKernelGGL((k_bwd_pass2<DT, ANISO>), dim3(blocks), dim3(kThreads), 0, s, a, g4, state, ctl, acc,
-                           small_off, small_n, split ? 1 : 0);
+                           small_off, small_n, sp);
     }
     if constexpr (ANISO) {
         AnisoAdj m{};

@@ -25,6 +25,10 @@ def dev(a):
     (9, 17, "five", False, True, "bf16", True, 3),
     (16, 23, "none", True, True, "f32", True, 2),
     (33, 15, "sixteen", True, True, "f32", False, 4),
+    # (1, 4, 8 and 16 waves for one cone in the scatter pass: by the waves of the frame)
+    (203, 210, "six", True, True, "f32", True, 1),
+    (150, 163, "six", True, True, "bf16", False, 1),
+    (105, 101, "six", True, True, "f16", True, 1),
 ])
 def test_small_frame_same_bits_as_in_a_large_one(h, w, cones, spec, occ, dtype, aniso, lights):
     n = 16
