@@ -47,8 +47,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass1(TraceArgs a, const fl
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ float s_part[kThreads / 64];
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     __syncthreads();
     const int tile = xcd_tile(blockIdx.x, a.n_tiles);
     int view, y, x;
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_trace_save(TraceArgs a, float4*
                                                          LaneState* __restrict__ state) {
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     __syncthreads();
     const int tile = xcd_tile(blockIdx.x, a.n_tiles);
     int view, y, x;
@@ -94,8 +94,8 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void k_trace_save_split(TraceA
     __shared__ DirSlot<ANISO> D;
     __shared__ float4 s_end[VCT_MAX_DIFFUSE + 2][64];
     __shared__ int s_next;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     if (threadIdx.x == 0) s_next = 0;
     __syncthreads();
     const Tile8 tl = tiles8(a);
@@ -552,8 +552,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ unsigned long long s_small[(ANISO ? kSmallMaxAniso : kSmallMax) * 4];
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<0>(a, &T);
+    load_dir_table<0>(a, &D);
     for (int i = threadIdx.x; i < small_n * 4; i += kThreads) s_small[i] = 0ull;
     __syncthreads();
     if (ctl[1] != 0) return;   // (a bound that is not finite: the gradient is NaN everywhere)

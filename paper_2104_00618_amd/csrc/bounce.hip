@@ -160,8 +160,8 @@ __global__ __launch_bounds__(1024) void k_gather(TraceArgs a, BounceArgs b) {
     __shared__ DirSlot<ANISO> D;
     __shared__ float s_c[VCT_MAX_DIFFUSE][3][64];
     __shared__ uint32_t s_tile;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     const uint32_t total = min(*b.total, 1u << (3 * b.lg));   // (the list holds at most n^3 entries)
     const uint32_t nt = (total + 63u) / 64u;
     const uint32_t per_xcd = (nt + 7u) / 8u;

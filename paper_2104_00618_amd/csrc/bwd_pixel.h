@@ -301,12 +301,12 @@ __device__ __forceinline__ LevelGeom level_geom(const LevelTable& T, int l, df U
     const Axis ax = axis_taps(Ux, sc, R.top);
     const Axis ay = axis_taps(Uy, sc, R.top);
     const Axis az = axis_taps(Uz, sc, R.top);
-    const uint32_t x0 = brick_x(ax.i0), y0 = brick_y(ay.i0, R.sy), z0 = brick_z(az.i0, R.sz);
+    const uint32_t x0 = brick_x<0>(ax.i0), y0 = brick_y<0>(ay.i0, R), z0 = brick_z<0>(az.i0, R.sz());
     LevelGeom g;
-    g.base = R.off + z0 + y0 + x0;
-    g.dx = brick_x(ax.i1) - x0;
-    g.dy = brick_y(ay.i1, R.sy) - y0;
-    g.dz = brick_z(az.i1, R.sz) - z0;
+    g.base = R.off() + z0 + y0 + x0;
+    g.dx = brick_x<0>(ax.i1) - x0;
+    g.dy = brick_y<0>(ay.i1, R) - y0;
+    g.dz = brick_z<0>(az.i1, R.sz()) - z0;
     g.wx = ax.w1;
     g.wy = ay.w1;
     g.wz = az.w1;

@@ -90,36 +90,68 @@ __device__ __forceinline__ float3 normalize3(float x, float y, float z) {
     return make_float3(x / r, y / r, z / r);
 }
 
+// Bits of 2^23: a whole number v < 2^23 plus 2^23 has the bits kOneUlp + v, so texel
+// coordinates become integers with an addition.
+constexpr uint32_t kOneUlp = 0x4b000000u;
+constexpr float k2p23 = 8388608.0f;
+
 // Shared-memory copy of the level table (per-lane levels index it; one 16-byte read).
 struct __align__(16) LevelRow {
-    float top;         // index of the last texel per axis (side - 1), as a float
-    uint32_t sy, sz;   // shifts of a brick's y and z coordinates in the index
-    uint32_t off;      // texel offset of the level
+    float top;         // index of the last texel per axis (side - 1)
+    float ys;          // a quarter of the index step of a brick along y
+    uint32_t ym;       // -(that step)
+    uint32_t off_sz;   // the level's offset, less what the three brick_ functions' sum has too much, and in the
+                       // six bits that this leaves zero log2 of the index step of a brick along z
+    __device__ __forceinline__ uint32_t off() const { return off_sz & ~63u; }
+    __device__ __forceinline__ uint32_t sz() const { return off_sz & 31u; }
 };
+
 struct LevelTable {
     LevelRow row[VCT_MAX_LEVELS];
 };
 
 // (Both table loaders stride over the workgroup, so they fill every entry for
 // any workgroup size; the caller synchronises before the tables are read.)
+// LOG: indexes and offsets are in units of 1 << LOG to the texel.
+template <int LOG>
 __device__ __forceinline__ void load_level_table(const TraceArgs& a, LevelTable* t) {
     for (int l = (int)threadIdx.x; l < VCT_MAX_LEVELS; l += (int)blockDim.x) {
         const uint32_t lnb = 31u - (uint32_t)__builtin_clz(a.lv[l].nb);   // log2 of bricks per axis
-        t->row[l] = {(float)(a.lv[l].n - 1), 6u + lnb, 6u + 2u * lnb, a.lv[l].off};
+        const uint32_t sz = 6u + LOG + 2u * lnb;
+        const uint32_t sy = 6u + LOG + lnb;
+        t->row[l] = {(float)(a.lv[l].n - 1), (float)(1u << (sy - 2u)), 0u - (1u << sy),
+                     ((a.lv[l].off << LOG) - 2u * kOneUlp - ((kOneUlp >> 2) << sz)) | sz};
     }
 }
 
-// Index contribution of a texel coordinate on each axis: the brick layout
-// ((bz * nb + by) * nb + bx) * 64 + (z & 3) * 16 + (y & 3) * 4 + (x & 3) is a sum over
-// the axes.  (As x + 60 (x >> 2) and so on, one shift and a 24-bit multiply-add, it is
-// fewer instructions and slower: 1.37 against 1.31 ms for the 1080p / 256^3 trace.)
-__device__ __forceinline__ uint32_t brick_x(int i) { return (uint32_t)(((i >> 2) << 6) | (i & 3)); }
-__device__ __forceinline__ uint32_t brick_y(int i, uint32_t sy) { return (uint32_t)(((i >> 2) << sy) | ((i & 3) << 2)); }
-__device__ __forceinline__ uint32_t brick_z(int i, uint32_t sz) { return (uint32_t)(((i >> 2) << sz) | ((i & 3) << 4)); }
+// Index contribution of a texel coordinate (a whole number from 0 to 1023) on each
+// axis: the brick layout ((bz * nb + by) * nb + bx) * 64 + (z & 3) * 16 + (y & 3) * 4 + (x & 3)
+// is a sum over the axes.  The marches are bound by VALU issue, and of its
+// instructions float add, multiply and FMA, integer add, AND, OR and right shifts with
+// vector or constant operands issue at 1.4 to 1.8 a CU-cycle here, all others
+// (left shifts, conversions, min / max, three-operand integer ones, and any with a
+// scalar register) at 0.9.  So the indexes are formed from the former where that is
+// no longer: x and y as float sums whose low bits are the integer, z (which can
+// pass 2^23) with its two left shifts.
+template <int LOG>
+__device__ __forceinline__ uint32_t brick_x(float x) {
+    const uint32_t b = __float_as_uint(__builtin_fmaf(x, (float)(16 << LOG), k2p23)) & ~((64u << LOG) - 1u);
+    return b + (__float_as_uint(__builtin_fmaf(x, (float)(1 << LOG), k2p23)) & (3u << LOG));
+}
+template <int LOG>
+__device__ __forceinline__ uint32_t brick_y(float y, const LevelRow& R) {
+    const uint32_t b = __float_as_uint(__builtin_fmaf(y, R.ys, k2p23)) & R.ym;
+    return b + (__float_as_uint(__builtin_fmaf(y, (float)(4 << LOG), k2p23)) & (12u << LOG));
+}
+template <int LOG>
+__device__ __forceinline__ uint32_t brick_z(float z, uint32_t sz) {
+    const uint32_t i = __float_as_uint(z + k2p23);
+    return ((i >> 2) << sz) + ((i & 3u) << (4 + LOG));
+}
 
 // Texel-space coordinate split into base tap and fraction, for level scale 2^-l.
 struct Axis {
-    int i0, i1;
+    float i0, i1;   // whole numbers
     float w1;  // weight of i1; i0 gets 1 - w1
 };
 
@@ -130,12 +162,12 @@ __device__ __forceinline__ Axis axis_taps(df U, float sc, float top) {
     float ph = (u - fl) + ulo;           // in (-1, 2): renormalise without branches
     float c = floorf(ph);
     ph -= c;
-    // clamp-to-edge in float before converting: both taps inside [0, top]; an
-    // integer-valued fi is exact below 2^24 and clamps to an edge above
+    // clamp-to-edge: both taps inside [0, top]; an integer-valued fi is exact
+    // below 2^24 and clamps to an edge above
     const float fi = fl + c;
     Axis a;
-    a.i0 = (int)__builtin_amdgcn_fmed3f(fi, 0.0f, top);
-    a.i1 = (int)__builtin_amdgcn_fmed3f(fi + 1.0f, 0.0f, top);
+    a.i0 = __builtin_amdgcn_fmed3f(fi, 0.0f, top);
+    a.i1 = __builtin_amdgcn_fmed3f(fi + 1.0f, 0.0f, top);
     a.w1 = ph;
     return a;
 }
@@ -150,20 +182,31 @@ struct Taps {
     }
 };
 
+// Units of the taps' indexes: byte offsets for the raw loads of 8-byte texels (a
+// pyramid they are used on has less than 4 GiB, so a side of at most 512), else texels.
+template <int DT>
+constexpr int kTapLog = DT == VCT_F16 || DT == VCT_BF16 ? 3 : 0;
+
 // The 8 taps and trilinear weights of level l at texel-space position U (level-0 texels).
+template <int LOG>
 __device__ __forceinline__ void level_taps(const LevelTable& T, int l, df Ux, df Uy, df Uz, Taps& tp) {
     const LevelRow R = T.row[l];
-    const float sc = __int_as_float((127 - l) << 23);   // 2^-l
+    float sc = __int_as_float((127 - l) << 23);   // 2^-l
+#ifndef VCT_HOST_EMULATION
+    // (a uniform level's scale, too, in a vector register: the float32 trace 1.43 -> 1.41 ms;
+    // slower for float16)
+    if constexpr (LOG == 0) asm("" : "+v"(sc));
+#endif
     Axis ax = axis_taps(Ux, sc, R.top);
     Axis ay = axis_taps(Uy, sc, R.top);
     Axis az = axis_taps(Uz, sc, R.top);
     const float wx0 = 1.0f - ax.w1, wy0 = 1.0f - ay.w1, wz0 = 1.0f - az.w1;
-    tp.x0 = brick_x(ax.i0);
-    tp.x1 = brick_x(ax.i1);
-    tp.y0 = brick_y(ay.i0, R.sy);
-    tp.y1 = brick_y(ay.i1, R.sy);
-    tp.z0 = R.off + brick_z(az.i0, R.sz);
-    tp.z1 = R.off + brick_z(az.i1, R.sz);
+    tp.x0 = brick_x<LOG>(ax.i0);
+    tp.x1 = brick_x<LOG>(ax.i1);
+    tp.y0 = brick_y<LOG>(ay.i0, R);
+    tp.y1 = brick_y<LOG>(ay.i1, R);
+    tp.z0 = R.off() + brick_z<LOG>(az.i0, R.sz());
+    tp.z1 = R.off() + brick_z<LOG>(az.i1, R.sz());
     const float wxy[4] = {wx0 * wy0, ax.w1 * wy0, wx0 * ay.w1, ax.w1 * ay.w1};
 #pragma unroll
     for (int q = 0; q < 8; ++q) tp.w[q] = wxy[q & 3] * ((q & 4) ? az.w1 : wz0);
@@ -181,11 +224,13 @@ template <bool ANISO>
 using DirSlot = typename std::conditional<ANISO, DirTable, NoDirTable>::type;
 __device__ __forceinline__ const DirTable* dir_ptr(const DirTable& t) { return &t; }
 __device__ __forceinline__ const DirTable* dir_ptr(const NoDirTable&) { return nullptr; }
+template <int LOG>
 __device__ __forceinline__ void load_dir_table(const TraceArgs&, NoDirTable*) {}
 
+template <int LOG>
 __device__ __forceinline__ void load_dir_table(const TraceArgs& a, DirTable* t) {
     for (int i = (int)threadIdx.x; i < 6 * VCT_MAX_LEVELS; i += (int)blockDim.x)
-        t->delta[i / VCT_MAX_LEVELS][i % VCT_MAX_LEVELS] = a.ddelta[i / VCT_MAX_LEVELS][i % VCT_MAX_LEVELS];
+        t->delta[i / VCT_MAX_LEVELS][i % VCT_MAX_LEVELS] = a.ddelta[i / VCT_MAX_LEVELS][i % VCT_MAX_LEVELS] << LOG;
 }
 
 // s += w * v on the four channels (the accumulation step of every gather).
@@ -273,18 +318,18 @@ __device__ __forceinline__ float4 gather(const TraceArgs& a, const Taps& tp) {
         // the second texel on their own, over the upper half of the pair.
         // (Texture-address requests per level: 4 plus those lanes' instead of
         // 8.)  Taps are accumulated in the order 0..7 of the other paths.
-        const bool apart = tp.x1 - tp.x0 != 1u;
+        const bool apart = tp.x1 - tp.x0 != 8u;
         vct_v4i pr[4];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            VCT_CHECK_TEXEL(tp.idx(2 * p));
-            pr[p] = vct_raw_load_v4i32(a.rraw, (int32_t)(tp.idx(2 * p) * 8u), 0, 0);
+            VCT_CHECK_TEXEL(tp.idx(2 * p) >> 3);
+            pr[p] = vct_raw_load_v4i32(a.rraw, (int32_t)tp.idx(2 * p), 0, 0);
         }
         if (apart) {
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                VCT_CHECK_TEXEL(tp.idx(2 * p + 1));
-                const vct_v2i u = vct_raw_load_v2i32(a.rraw, (int32_t)(tp.idx(2 * p + 1) * 8u), 0, 0);
+                VCT_CHECK_TEXEL(tp.idx(2 * p + 1) >> 3);
+                const vct_v2i u = vct_raw_load_v2i32(a.rraw, (int32_t)tp.idx(2 * p + 1), 0, 0);
                 pr[p].z = u.x;
                 pr[p].w = u.y;
             }
@@ -436,7 +481,7 @@ template <int DT, bool ANISO, bool SHARE = false>
 __device__ __forceinline__ float4 level_sample(const TraceArgs& a, const LevelTable& T, const DirTable* D,
                                                const Cone& c, int l, df Ux, df Uy, df Uz) {
     Taps tp;
-    level_taps(T, l, Ux, Uy, Uz, tp);
+    level_taps<kTapLog<DT>>(T, l, Ux, Uy, Uz, tp);
     if constexpr (ANISO) {
         if (l > 0) {
             const float W[3] = {c.Wx, c.Wy, c.Wz};

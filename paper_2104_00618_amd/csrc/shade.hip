@@ -28,8 +28,8 @@ __global__ __launch_bounds__(256) void k_shade(TraceArgs a, ShadeArgs s, float4*
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ unsigned long long s_cnt;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     if (COUNT && threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
     const int tile = xcd_tile(blockIdx.x, a.n_tiles);
@@ -55,14 +55,14 @@ __global__ __launch_bounds__(256) void k_shade(TraceArgs a, ShadeArgs s, float4*
 // The shading of small frames (Tile8 in march.h): items are the specular cone,
 // the lights' occlusion cones, then the diffuse cones.
 template <int DT, bool ANISO>
-__global__ __launch_bounds__(64 * kSplitWaves) void k_shade_split(TraceArgs a, ShadeArgs s, float4* __restrict__ out) {
+__global__ __launch_bounds__(64 * kSplitWaves, 4) void k_shade_split(TraceArgs a, ShadeArgs s, float4* __restrict__ out) {
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ float s_col[VCT_MAX_DIFFUSE + 1][3][64];   // specular, diffuse
     __shared__ float s_occ[VCT_MAX_LIGHTS][64];
     __shared__ int s_next;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     if (threadIdx.x == 0) s_next = 0;
     __syncthreads();
     const Tile8 tl = tiles8(a);

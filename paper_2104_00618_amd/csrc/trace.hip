@@ -22,8 +22,8 @@ __global__ __launch_bounds__(256) void k_trace(TraceArgs a, float4* __restrict__
     __shared__ LevelTable T;
     __shared__ DirSlot<ANISO> D;
     __shared__ unsigned long long s_cnt[2];
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     if (COUNT && threadIdx.x < 2) s_cnt[threadIdx.x] = 0;
     __syncthreads();
 
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_trace_split(TraceArgs a, f
     __shared__ DirSlot<ANISO> D;
     __shared__ float4 s_end[VCT_MAX_DIFFUSE + 2][64];
     __shared__ int s_next;
-    load_level_table(a, &T);
-    load_dir_table(a, &D);
+    load_level_table<kTapLog<DT>>(a, &T);
+    load_dir_table<kTapLog<DT>>(a, &D);
     if (threadIdx.x == 0) s_next = 0;
     __syncthreads();
     const Tile8 tl = tiles8(a);
