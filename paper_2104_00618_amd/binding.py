@@ -6,10 +6,12 @@ raises: there is no fallback path.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
 
+import numpy as np
 import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -241,18 +243,22 @@ def voxelize_params(lights, ambient=0.1, diffuse=1.0):
     return c
 
 
+def _rows(v):
+    """v as something that iterates fast (an array's or a tensor's elements one by one do not)."""
+    return v.tolist() if isinstance(v, (np.ndarray, torch.Tensor)) else v
+
+
 def cone_params(p):
     """C struct from any object with the cone-set attributes (n_diffuse taken
     from len(diffuse_dirs))."""
     c = CConeParams()
-    dirs = [tuple(map(float, d)) for d in p.diffuse_dirs]
-    wts = [float(w) for w in p.diffuse_weights]
+    dirs = [tuple(map(float, d)) for d in _rows(p.diffuse_dirs)]
+    wts = [float(w) for w in _rows(p.diffuse_weights)]
     if len(dirs) > MAX_DIFFUSE or len(wts) != len(dirs):
         raise ValueError("diffuse_dirs / diffuse_weights: at most 16 cones, one weight per direction")
     c.n_diffuse = len(dirs)
     for q, d in enumerate(dirs):
-        for i in range(3):
-            c.diffuse_dir[q][i] = d[i]
+        c.diffuse_dir[q][:] = (d[0], d[1], d[2])
         c.diffuse_weight[q] = wts[q]
     c.diffuse_aperture = float(p.diffuse_aperture)
     c.enable_spec = int(bool(p.enable_spec))
@@ -273,6 +279,14 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
 
 
+_SAME_DEVICE = contextlib.nullcontext()
+
+
+def _on(dev):
+    """torch.cuda.device(dev), which costs more than most calls' own work, only where it changes the device."""
+    return _SAME_DEVICE if torch.cuda.current_device() == dev.index else torch.cuda.device(dev)
+
+
 def _stream(dev):
     return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
 
@@ -288,7 +302,7 @@ def _need(t, name, dtype, shape=None, device=None):
         raise ValueError(f"{name} is on {t.device}, expected {device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
@@ -324,7 +338,7 @@ def build_mips(base, grid, pyramid=None):
     if pyramid is None:
         pyramid = torch.empty(nb, dtype=torch.uint8, device=base.device)
     _need(pyramid, "pyramid", torch.uint8, None, base.device)
-    with torch.cuda.device(base.device):
+    with _on(base.device):
         _check(lib().vct_build_mips(ctypes.byref(grid.c()), _ptr(base), _ptr(pyramid), pyramid.numel(),
                                     _stream(base.device)))
     return pyramid
@@ -333,7 +347,7 @@ def build_mips(base, grid, pyramid=None):
 def unpack_level(pyramid, grid, level):
     nl = grid.n >> level
     out = torch.empty((nl, nl, nl, 4), dtype=torch.float32, device=pyramid.device)
-    with torch.cuda.device(pyramid.device):
+    with _on(pyramid.device):
         _check(lib().vct_unpack_level(ctypes.byref(grid.c()), _ptr(pyramid), int(level), _ptr(out),
                                       _stream(pyramid.device)))
     return out
@@ -344,7 +358,7 @@ def unpack_level_dir(pyramid, grid, level, direction):
     of an anisotropic pyramid as float32 [N_l, N_l, N_l, 4]."""
     nl = grid.n >> level
     out = torch.empty((nl, nl, nl, 4), dtype=torch.float32, device=pyramid.device)
-    with torch.cuda.device(pyramid.device):
+    with _on(pyramid.device):
         _check(lib().vct_unpack_level_dir(ctypes.byref(grid.c()), _ptr(pyramid), int(level), int(direction),
                                           _ptr(out), _stream(pyramid.device)))
     return out
@@ -357,7 +371,7 @@ def trace(pyramid, grid, pos_rough, normal, cam_pos, params, out=None):
     if out is None:
         out = torch.empty(tuple(pos_rough.shape[:3]) + (8,), dtype=torch.float32, device=pos_rough.device)
     _need(out, "out", torch.float32, tuple(pos_rough.shape[:3]) + (8,), pos_rough.device)
-    with torch.cuda.device(pos_rough.device):
+    with _on(pos_rough.device):
         _check(lib().vct_trace(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
                                ctypes.byref(cone_params(params)), _ptr(out), _stream(pos_rough.device)))
     return out
@@ -373,7 +387,7 @@ def shade(pyramid, grid, pos_rough, normal, cam_pos, material, params, sparams, 
     if out is None:
         out = torch.empty(tuple(pos_rough.shape[:3]) + (4,), dtype=torch.float32, device=dev)
     _need(out, "out", torch.float32, tuple(pos_rough.shape[:3]) + (4,), dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_shade(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb), _ptr(material),
                                ctypes.byref(cone_params(params)), ctypes.byref(shade_params(sparams)), _ptr(out),
                                _stream(dev)))
@@ -388,7 +402,7 @@ def count_shade_samples(pyramid, grid, pos_rough, normal, cam_pos, material, par
     _need(pyramid, "pyramid", torch.uint8, None, dev)
     _need(material, "material", torch.float32, tuple(pos_rough.shape), dev)
     cnt = torch.zeros(1, dtype=torch.int64, device=dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_count_shade_samples(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb), _ptr(material),
                                              ctypes.byref(cone_params(params)), ctypes.byref(shade_params(sparams)),
                                              _ptr(cnt), _stream(dev)))
@@ -425,7 +439,7 @@ def voxelize(tris, colors, grid, lights, ambient=0.1, diffuse=1.0, base=None, wo
         workspace = torch.empty(voxelize_workspace_bytes(grid, tris.shape[0], surface), dtype=torch.uint8,
                                 device=dev)
     _need(workspace, "workspace", torch.uint8, None, dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_voxelize(ctypes.byref(grid.c()), _ptr(tris), _ptr(colors), int(tris.shape[0]),
                                   ctypes.byref(voxelize_params(lights, ambient, diffuse)), _ptr(base),
                                   _ptr(normal), _ptr(albedo), _ptr(workspace), workspace.numel(), _stream(dev)))
@@ -454,7 +468,7 @@ def bounce(pyramid, grid, base, normal, albedo, params, out=None, workspace=None
     if workspace is None:
         workspace = torch.empty(bounce_workspace_bytes(grid), dtype=torch.uint8, device=dev)
     _need(workspace, "workspace", torch.uint8, None, dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_bounce(ctypes.byref(grid.c()), _ptr(pyramid), _ptr(base), _ptr(normal), _ptr(albedo),
                                 ctypes.byref(cone_params(params)), _ptr(out), _ptr(workspace), workspace.numel(),
                                 _stream(dev)))
@@ -465,7 +479,7 @@ def count_samples(pyramid, grid, pos_rough, normal, cam_pos, params):
     """Total cone samples the forward march takes (integer, exact)."""
     gb = _gbuf(pos_rough, normal, cam_pos)
     cnt = torch.zeros(1, dtype=torch.int64, device=pos_rough.device)
-    with torch.cuda.device(pos_rough.device):
+    with _on(pos_rough.device):
         _check(lib().vct_count_samples(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
                                        ctypes.byref(cone_params(params)), _ptr(cnt), _stream(pos_rough.device)))
     return int(cnt.item())
@@ -475,7 +489,7 @@ def count_sample_levels(pyramid, grid, pos_rough, normal, cam_pos, params):
     """(all cone samples, samples that read two levels) of the forward march."""
     gb = _gbuf(pos_rough, normal, cam_pos)
     cnt = torch.zeros(2, dtype=torch.int64, device=pos_rough.device)
-    with torch.cuda.device(pos_rough.device):
+    with _on(pos_rough.device):
         _check(lib().vct_count_sample_levels(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
                                              ctypes.byref(cone_params(params)), _ptr(cnt),
                                              _stream(pos_rough.device)))
@@ -483,12 +497,25 @@ def count_sample_levels(pyramid, grid, pos_rough, normal, cam_pos, params):
     return int(c[0]), int(c[1])
 
 
+# (The C structs are made once in a call and handed on: with three conversions of the
+# G-buffer and the cones in each backward and two in each forward, the host took 214 us
+# of a 16^3 training pass whose kernels take 125.)
+
+def _backward_workspace_bytes(g, gb, cp):
+    n = ctypes.c_size_t()
+    _check(lib().vct_backward_workspace_bytes(ctypes.byref(g), ctypes.byref(gb), ctypes.byref(cp), ctypes.byref(n)))
+    return n.value
+
+
+def _lane_state_bytes(gb, cp):
+    n = ctypes.c_size_t()
+    _check(lib().vct_lane_state_bytes(ctypes.byref(gb), ctypes.byref(cp), ctypes.byref(n)))
+    return n.value
+
+
 def backward_workspace_bytes(grid, pos_rough, normal, cam_pos, params):
     gb = _gbuf(pos_rough, normal, cam_pos)
-    n = ctypes.c_size_t()
-    _check(lib().vct_backward_workspace_bytes(ctypes.byref(grid.c()), ctypes.byref(gb),
-                                              ctypes.byref(cone_params(params)), ctypes.byref(n)))
-    return n.value
+    return _backward_workspace_bytes(grid.c(), gb, cone_params(params))
 
 
 def trace_backward(pyramid, grid, pos_rough, normal, cam_pos, params, grad_out, workspace=None, grad_base=None):
@@ -496,25 +523,24 @@ def trace_backward(pyramid, grid, pos_rough, normal, cam_pos, params, grad_out, 
     gb = _gbuf(pos_rough, normal, cam_pos)
     dev = pos_rough.device
     _need(grad_out, "grad_out", torch.float32, tuple(pos_rough.shape[:3]) + (8,), dev)
-    nbytes = backward_workspace_bytes(grid, pos_rough, normal, cam_pos, params)
+    g, cp = grid.c(), cone_params(params)
+    nbytes = _backward_workspace_bytes(g, gb, cp)
     if workspace is None:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     _need(workspace, "workspace", torch.uint8, None, dev)
     if grad_base is None:
         grad_base = torch.empty((grid.n, grid.n, grid.n, 4), dtype=torch.float32, device=dev)
     _need(grad_base, "grad_base", torch.float32, (grid.n, grid.n, grid.n, 4), dev)
-    with torch.cuda.device(dev):
-        _check(lib().vct_trace_backward(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
-                                        ctypes.byref(cone_params(params)), _ptr(grad_out), _ptr(grad_base),
+    with _on(dev):
+        _check(lib().vct_trace_backward(ctypes.byref(g), _ptr(pyramid), ctypes.byref(gb),
+                                        ctypes.byref(cp), _ptr(grad_out), _ptr(grad_base),
                                         _ptr(workspace), workspace.numel(), _stream(dev)))
     return grad_base
 
 
 def lane_state_bytes(pos_rough, normal, cam_pos, params):
     gb = _gbuf(pos_rough, normal, cam_pos)
-    n = ctypes.c_size_t()
-    _check(lib().vct_lane_state_bytes(ctypes.byref(gb), ctypes.byref(cone_params(params)), ctypes.byref(n)))
-    return n.value
+    return _lane_state_bytes(gb, cone_params(params))
 
 
 def trace_save(pyramid, grid, pos_rough, normal, cam_pos, params, out=None, lane_state=None):
@@ -524,12 +550,13 @@ def trace_save(pyramid, grid, pos_rough, normal, cam_pos, params, out=None, lane
     if out is None:
         out = torch.empty(tuple(pos_rough.shape[:3]) + (8,), dtype=torch.float32, device=dev)
     _need(out, "out", torch.float32, tuple(pos_rough.shape[:3]) + (8,), dev)
+    cp = cone_params(params)
     if lane_state is None:
-        lane_state = torch.empty(lane_state_bytes(pos_rough, normal, cam_pos, params), dtype=torch.uint8, device=dev)
+        lane_state = torch.empty(_lane_state_bytes(gb, cp), dtype=torch.uint8, device=dev)
     _need(lane_state, "lane_state", torch.uint8, None, dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_trace_save(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
-                                    ctypes.byref(cone_params(params)), _ptr(out), _ptr(lane_state),
+                                    ctypes.byref(cp), _ptr(out), _ptr(lane_state),
                                     lane_state.numel(), _stream(dev)))
     return out, lane_state
 
@@ -541,17 +568,17 @@ def trace_backward_saved(pyramid, grid, pos_rough, normal, cam_pos, params, lane
     dev = pos_rough.device
     _need(grad_out, "grad_out", torch.float32, tuple(pos_rough.shape[:3]) + (8,), dev)
     _need(lane_state, "lane_state", torch.uint8, None, dev)
-    nbytes = backward_workspace_bytes(grid, pos_rough, normal, cam_pos, params) - lane_state_bytes(
-        pos_rough, normal, cam_pos, params)
+    g, cp = grid.c(), cone_params(params)
+    nbytes = _backward_workspace_bytes(g, gb, cp) - _lane_state_bytes(gb, cp)
     if workspace is None:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     _need(workspace, "workspace", torch.uint8, None, dev)
     if grad_base is None:
         grad_base = torch.empty((grid.n, grid.n, grid.n, 4), dtype=torch.float32, device=dev)
     _need(grad_base, "grad_base", torch.float32, (grid.n, grid.n, grid.n, 4), dev)
-    with torch.cuda.device(dev):
-        _check(lib().vct_trace_backward_saved(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
-                                              ctypes.byref(cone_params(params)), _ptr(lane_state), lane_state.numel(),
+    with _on(dev):
+        _check(lib().vct_trace_backward_saved(ctypes.byref(g), _ptr(pyramid), ctypes.byref(gb),
+                                              ctypes.byref(cp), _ptr(lane_state), lane_state.numel(),
                                               _ptr(grad_out), _ptr(grad_base), _ptr(workspace), workspace.numel(),
                                               _stream(dev)))
     return grad_base
@@ -569,7 +596,7 @@ def trace_backward_saved_noalloc(pyramid, grid, pos_rough, normal, cam_pos, para
     _need(grad_out, "grad_out", torch.float32, tuple(pos_rough.shape[:3]) + (8,), dev)
     _need(lane_state, "lane_state", torch.uint8, None, dev)
     _need(grad_base, "grad_base", torch.float32, (grid.n, grid.n, grid.n, 4), dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(lib().vct_trace_backward_saved_noalloc(ctypes.byref(grid.c()), _ptr(pyramid), ctypes.byref(gb),
                                                       ctypes.byref(cone_params(params)), _ptr(lane_state),
                                                       lane_state.numel(), _ptr(grad_out), _ptr(grad_base),
