@@ -30,7 +30,7 @@
 //
 // Anisotropic pyramids (Section 5.1.3) use the same kernels instantiated for
 // six directional pyramids: every level accumulates at the scale 2^E, and
-// k_aniso_adjoint, one launch per level from the top, replaces k_mip_adjoint
+// k_aniso_adjoint, level by level from the top, replaces k_mip_adjoint
 // (the adjoint of a directional texel depends on the stored texels, so it is
 // no longer a fixed factor per level).
 #include "bwd_pixel.h"
@@ -718,8 +718,8 @@ __global__ __launch_bounds__(256) void k_mip_adjoint(AdjArgs m, const long long*
     }
 }
 
-// Mip adjoint of anisotropic pyramids, one launch per level from the top
-// down.  The gradient of a directional texel is its own accumulated sum plus
+// Mip adjoint of anisotropic pyramids, level by level from the top
+// down (the coarse levels in one launch, then a launch for each).  The gradient of a directional texel is its own accumulated sum plus
 // what its parent (same direction, one level up) passes through the
 // linearised front-to-back composite: parent = (1/4) sum over the four child
 // pairs along the direction's axis of over(f, b) = f + (1 - f.a) b, so the
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(256) void k_mip_adjoint(AdjArgs m, const long long*
 // per slot, parents final before their children run); level 0 sums the six
 // directions' contributions in order and writes the base gradient.
 struct AnisoAdj {
-    int32_t n, levels, level;          // level processed (its parents are level + 1)
+    int32_t n, levels;
     int32_t nb[VCT_MAX_LEVELS];
     uint32_t doff[6][VCT_MAX_LEVELS];
 };
@@ -742,9 +742,9 @@ __device__ __forceinline__ float4 scaled(const long long* p, int E) {
 }
 
 template <int DT>
-__device__ __forceinline__ float4 from_parent(const AnisoAdj& m, const void* pyr, const long long* acc, int d, int x,
-                                              int y, int z) {
-    const int c = m.level, nbp = m.nb[c + 1];
+__device__ __forceinline__ float4 from_parent(const AnisoAdj& m, int c, const void* pyr, const long long* acc, int d,
+                                              int x, int y, int z) {
+    const int nbp = m.nb[c + 1];
     const float4 G = *reinterpret_cast<const float4*>(
         acc + (size_t)(m.doff[d][c + 1] + vct_brick_index(x >> 1, y >> 1, z >> 1, nbp)) * 4);
     const int axis = d >> 1;
@@ -760,25 +760,18 @@ __device__ __forceinline__ float4 from_parent(const AnisoAdj& m, const void* pyr
     return make_float4(t * G.x, t * G.y, t * G.z, t * G.w);
 }
 
+// Texel (x, y, z) of level c, directions d0 .. d1 - 1 (level 0: all six at once).
 template <int DT>
-__global__ __launch_bounds__(256) void k_aniso_adjoint(AnisoAdj m, long long* __restrict__ acc, const void* pyr,
-                                                       const int* __restrict__ ctl, float4* __restrict__ grad) {
-    const int E = ctl[0];
-    const bool bad = ctl[1] != 0;
-    const int c = m.level, side = m.n >> c, nb = m.nb[c];
+__device__ __forceinline__ void aniso_adjoint_texel(const AnisoAdj& m, int c, long long* __restrict__ acc, const void* pyr,
+                                                    int E, bool bad, float4* __restrict__ grad, int x, int y, int z,
+                                                    int d0, int d1) {
     const bool top = c == m.levels - 1;
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t brick = t >> 6, w = t & 63u;
-    if (brick >= (uint32_t)nb * nb * nb) return;
-    const int x = (int)(brick % nb) * 4 + (int)(w & 3u), y = (int)((brick / nb) % nb) * 4 + (int)((w >> 2) & 3u),
-              z = (int)(brick / ((uint32_t)nb * nb)) * 4 + (int)(w >> 4);
-    if (x >= side || y >= side || z >= side) return;
-    const uint32_t at = vct_brick_index(x, y, z, nb);
+    const uint32_t at = vct_brick_index(x, y, z, m.nb[c]);
     if (c == 0) {
         float4 g = scaled(acc + (size_t)at * 4, E);
         if (!top)
             for (int d = 0; d < 6; ++d) {
-                const float4 p = from_parent<DT>(m, pyr, acc, d, x, y, z);
+                const float4 p = from_parent<DT>(m, c, pyr, acc, d, x, y, z);
                 g.x += p.x;
                 g.y += p.y;
                 g.z += p.z;
@@ -789,17 +782,51 @@ __global__ __launch_bounds__(256) void k_aniso_adjoint(AnisoAdj m, long long* __
         grad[((size_t)z * m.n + y) * m.n + x] = g;
         return;
     }
-    for (int d = 0; d < 6; ++d) {
+    for (int d = d0; d < d1; ++d) {
         long long* slot = acc + (size_t)(m.doff[d][c] + at) * 4;
         float4 g = scaled(slot, E);
         if (!top) {
-            const float4 p = from_parent<DT>(m, pyr, acc, d, x, y, z);
+            const float4 p = from_parent<DT>(m, c, pyr, acc, d, x, y, z);
             g.x += p.x;
             g.y += p.y;
             g.z += p.z;
             g.w += p.w;
         }
         *reinterpret_cast<float4*>(slot) = g;
+    }
+}
+
+// Level c, one thread per texel, brick by brick.
+template <int DT>
+__global__ __launch_bounds__(256) void k_aniso_adjoint(AnisoAdj m, int c, long long* __restrict__ acc, const void* pyr,
+                                                       const int* __restrict__ ctl, float4* __restrict__ grad) {
+    const int side = m.n >> c, nb = m.nb[c];
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t brick = t >> 6, w = t & 63u;
+    if (brick >= (uint32_t)nb * nb * nb) return;
+    const int x = (int)(brick % nb) * 4 + (int)(w & 3u), y = (int)((brick / nb) % nb) * 4 + (int)((w >> 2) & 3u),
+              z = (int)(brick / ((uint32_t)nb * nb)) * 4 + (int)(w >> 4);
+    if (x >= side || y >= side || z >= side) return;
+    aniso_adjoint_texel<DT>(m, c, acc, pyr, ctl[0], ctl[1] != 0, grad, x, y, z, 0, 6);
+}
+
+// The levels from the top down to `first` (side at most VCT_ANISO_COARSE_SIDE) in one
+// workgroup, a thread per texel and direction: as launches of their own they take 5 us
+// each for at most 512 texels.
+template <int DT>
+__global__ __launch_bounds__(1024) void k_aniso_adjoint_coarse(AnisoAdj m, int first, long long* __restrict__ acc,
+                                                               const void* pyr, const int* __restrict__ ctl,
+                                                               float4* __restrict__ grad) {
+    const int E = ctl[0];
+    const bool bad = ctl[1] != 0;
+    for (int c = m.levels - 1; c >= first; --c) {
+        const int lg = 31 - __builtin_clz(m.n >> c), mask = (1 << lg) - 1;
+        const int items = (c == 0 ? 1 : 6) << (3 * lg);
+        for (int i = (int)threadIdx.x; i < items; i += 1024) {
+            const int d = i >> (3 * lg);
+            aniso_adjoint_texel<DT>(m, c, acc, pyr, E, bad, grad, i & mask, (i >> lg) & mask, (i >> (2 * lg)) & mask, d, d + 1);
+        }
+        __syncthreads();
     }
 }
 
@@ -863,10 +890,13 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
             for (int d = 0; d < 6; ++d) m.doff[d][l] = (uint32_t)L.doff[d][l];
         }
         es.mark(s);
-        for (int c = L.levels - 1; c >= 0; --c) {
-            m.level = c;
+        const int first = vct_aniso_coarse(L, 0);
+        if (first < L.levels)
+            hipLaunchKernelGGL(k_aniso_adjoint_coarse<DT>, dim3(1), dim3(1024), 0, s, m, first,
+                               reinterpret_cast<long long*>(acc), a.pyr, ctl, reinterpret_cast<float4*>(grad_base));
+        for (int c = first - 1; c >= 0; --c) {
             const uint32_t threads = (uint32_t)L.nb[c] * L.nb[c] * L.nb[c] * 64u;
-            hipLaunchKernelGGL(k_aniso_adjoint<DT>, dim3((threads + 255u) / 256u), dim3(256), 0, s, m,
+            hipLaunchKernelGGL(k_aniso_adjoint<DT>, dim3((threads + 255u) / 256u), dim3(256), 0, s, m, c,
                                reinterpret_cast<long long*>(acc), a.pyr, ctl, reinterpret_cast<float4*>(grad_base));
         }
         es.mark(s);

@@ -94,6 +94,15 @@ static inline PyrLayout vct_make_layout(int n, int levels, int dtype, int aniso 
     return p;
 }
 
+// Anisotropic mips and their adjoint take the levels of at most this side in one workgroup.
+#define VCT_ANISO_COARSE_SIDE 8
+// The first of those levels, from level `from` on (L.levels if there is none).
+static inline int vct_aniso_coarse(const PyrLayout& L, int from) {
+    int l = from;
+    while (l < L.levels && (L.n >> l) > VCT_ANISO_COARSE_SIDE) ++l;
+    return l;
+}
+
 // Texel index inside a level (brick layout above).
 __host__ __device__ static inline uint32_t vct_brick_index(int x, int y, int z, int nb) {
     return (uint32_t)((((z >> 2) * nb + (y >> 2)) * nb + (x >> 2)) << 6) +
