@@ -723,7 +723,8 @@ __global__ __launch_bounds__(256) void k_mip_adjoint(AdjArgs m, const long long*
 }
 
 // Mip adjoint of anisotropic pyramids, level by level from the top
-// down (the coarse levels in one launch, then a launch for each).  The gradient of a directional texel is its own accumulated sum plus
+// down (the coarse levels in one launch, then a launch for each).  The gradient
+// of a directional texel is its own accumulated sum plus
 // what its parent (same direction, one level up) passes through the
 // linearised front-to-back composite: parent = (1/4) sum over the four child
 // pairs along the direction's axis of over(f, b) = f + (1 - f.a) b, so the
