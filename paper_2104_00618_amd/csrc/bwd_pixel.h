@@ -272,6 +272,9 @@ struct Pass2Lane {
 };
 
 // Set up the re-march of cone `slot`; K = 0 when the cone receives no gradient.
+// The cone has to be bit for bit the one whose end state S is: one of which an axis
+// differs in its last bit can reach A = 1 before its last sample, where the
+// gradient divides by 1 - A.
 __device__ __forceinline__ void pass2_init(const TraceArgs& a, const PixelSetup& P, float3 cam, float4 g0, float4 g1,
                                            const LaneState& S, int slot, Pass2Lane& L) {
     slot_grads(a, slot, g0, g1, L.gc, L.ga);
@@ -281,7 +284,7 @@ __device__ __forceinline__ void pass2_init(const TraceArgs& a, const PixelSetup&
     L.R[1] = {S.hi.y, S.lo.y};
     L.R[2] = {S.hi.z, S.lo.z};
     L.TK = 1.0f - S.hi.w;
-    L.c = cone_for_slot(a, P, slot, cam);
+    L.c = cone_for_slot<true>(a, P, slot, cam);
     L.A = 0.f;
     L.t = {a.t0, 0.0f};
 }

@@ -443,10 +443,10 @@ __device__ __forceinline__ float3 reflect3(float3 v, const PixelSetup& P) {
 
 // Axis of cone slot `slot` of a pixel (0..u-1 diffuse, u specular, u+1 occlusion);
 // sets aperture and t_max.  (VIEW_X_FIRST: rounding of the view vector's length in
-// the forward that keeps lane states, pass 1 of the backward with it.  The re-march and
-// the plain trace round it the other way round, so specular axes off the coordinate
-// axes can differ in their last bit, which a saturating cone's gradient shows; both
-// roundings are kept as they were, so that results are.)
+// the forward that keeps lane states, and so in pass 1 and in the re-march of the
+// scatter pass, whose samples have to be that forward's.  The plain trace rounds it
+// the other way round, so its specular axes off the coordinate axes can differ from
+// theirs in the last bit.)
 template <bool VIEW_X_FIRST = false>
 __device__ __forceinline__ Cone cone_for_slot(const TraceArgs& a, const PixelSetup& P, int slot, float3 cam) {
     if (slot < a.n_diffuse) {
