@@ -142,11 +142,13 @@ __device__ __forceinline__ Pass1Out pass1_march(const TraceArgs& a, const LevelT
 //   alpha = sum_k |T_k| + sum_{k<K-1} |T_k / T_{k+1}| (|C_K| + max_k |C_k|),
 //   beta  = sum_{k<K-1} |T_k / T_{k+1}| |T_K| + |T_{K-1}|  (K > 0),
 // which the forward stores so that the backward's bound pass reads 8 bytes
-// per cone.
+// per cone.  A colour that is not finite in any channel makes alpha NaN (fmaxf would
+// pass over a NaN beside a number), and so the whole gradient.
 __device__ __forceinline__ float2 lane_coefs(const Pass1Out& r) {
     const float CK = fmaxf(fabsf(r.C[0].hi), fmaxf(fabsf(r.C[1].hi), fabsf(r.C[2].hi)));
     const float TK = 1.0f - r.A;
-    const float alpha = r.ST + r.SQ * (CK + r.MC);
+    const float not_finite = (r.C[0].hi * 0.0f + r.C[1].hi * 0.0f) + r.C[2].hi * 0.0f;   // 0, or NaN
+    const float alpha = r.ST + r.SQ * (CK + r.MC) + not_finite;
     const float beta = r.SQ * fabsf(TK) + (r.K > 0 ? fabsf(r.Tlast) : 0.f);
     return make_float2(alpha, beta);
 }

@@ -25,8 +25,21 @@ def _grid(n, what):
 @pytest.mark.parametrize("aniso", [False, True])
 @pytest.mark.parametrize("dtype,what", [("f16", "one texel"), ("f16", "red"), ("f32", "nan")])
 def test_scatter_stays_in_the_accumulator(checked, tmp_path, dtype, what, aniso, levels):  # noqa: F811
+    _backward(checked, tmp_path, dtype, what, aniso, levels)
+
+
+@pytest.mark.parametrize("aniso", [False, True])
+@pytest.mark.parametrize("dtype,what", [("f16", "one texel"), ("f16", "red"), ("f32", "nan")])
+def test_a_colour_that_is_not_finite_shows_in_the_gradient(checked, tmp_path, dtype, what, aniso):  # noqa: F811
+    """One such channel of one cone is enough, as where all three are: the gradient is NaN everywhere."""
+    res = _backward(checked, tmp_path, dtype, what, aniso, None)
+    assert not np.isfinite(res["save"]).all()
+    assert np.isnan(res["grad"]).all()
+
+
+def _backward(checked, tmp_path, dtype, what, aniso, levels):  # noqa: F811
     n = 8
     pr, nr, cam = random_gbuffer(1, 8, 8, seed=6, n=n)
     gout = np.random.default_rng(7).normal(size=(1, 8, 8, 8)).astype(np.float32)
-    run_case(checked, str(tmp_path), _grid(n, what), pr, nr, cam, _params(), dtype=dtype, aniso=aniso, levels=levels,
-             gout=gout)
+    return run_case(checked, str(tmp_path), _grid(n, what), pr, nr, cam, _params(), dtype=dtype, aniso=aniso,
+                    levels=levels, gout=gout)
