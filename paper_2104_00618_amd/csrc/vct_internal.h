@@ -157,8 +157,13 @@ struct TraceArgs {
 // The scatter pass has nothing to join, and its longer chains gain up to larger
 // frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1951 -> 1864 at 1280 x 720,
 // 4594 -> 4637 at 1920 x 1080 (8160).
-static inline bool vct_split_forward(const TraceArgs& a) { return a.n_tiles <= 768; }
-static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= 4096; }
+// (The limits are hooks: a host-emulation build runs either kernel on any frame.)
+#ifndef VCT_SPLIT_FORWARD_TILES
+#define VCT_SPLIT_FORWARD_TILES 768
+#define VCT_SPLIT_SCATTER_TILES 4096
+#endif
+static inline bool vct_split_forward(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_FORWARD_TILES; }
+static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_SCATTER_TILES; }
 
 // Calls f(std::integral_constant<int, DT>) with the kernel template argument
 // of a pyramid: its storage type, plus VCT_WIDE when it needs 64-bit fetches.

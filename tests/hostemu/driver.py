@@ -10,7 +10,7 @@ DTYPES = {"f32": 0, "f16": 1, "bf16": 2}
 
 def run_case(binary, d, base, pr, nr, cam, p, dtype="f32", levels=None, aniso=False, gout=None, backward=True,
              noalloc=False, n=None, block_origin=0, bounce=None, save_only=False,
-             dump_levels=False, shade=None, material=None, origin=(0.0, 0.0, 0.0), extent=1.0, timeout=600):
+             dump_levels=False, recompute=False, shade=None, material=None, origin=(0.0, 0.0, 0.0), extent=1.0, timeout=600):
     os.makedirs(d, exist_ok=True)
     # (block_origin w0: `base` is the corner block [w0, n)^3 of an n^3 grid that is zero elsewhere)
     n = n or base.shape[0]
@@ -23,7 +23,8 @@ def run_case(binary, d, base, pr, nr, cam, p, dtype="f32", levels=None, aniso=Fa
                 light0=p.light_pos[0], light1=p.light_pos[1], light2=p.light_pos[2], step_factor=p.step_factor,
                 t0=p.t0, normal_offset=p.normal_offset, max_dist=p.max_dist, alpha_thresh=p.alpha_thresh,
                 backward=int(backward), noalloc=int(noalloc), dump_levels=int(dump_levels), block_origin=block_origin,
-                shade=int(shade is not None), bounce=int(bounce is not None), save_only=int(save_only))
+                shade=int(shade is not None), bounce=int(bounce is not None), save_only=int(save_only),
+                recompute=int(recompute))
     np.ascontiguousarray(base, np.float32).tofile(f"{d}/base.bin")
     np.ascontiguousarray(pr, np.float32).tofile(f"{d}/pos_rough.bin")
     np.ascontiguousarray(nr, np.float32).tofile(f"{d}/normal.bin")
@@ -60,6 +61,8 @@ def run_case(binary, d, base, pr, nr, cam, p, dtype="f32", levels=None, aniso=Fa
         res["grad"] = np.fromfile(f"{d}/grad.bin", np.float32).reshape(m, m, m, 4)
         if block_origin:
             res["grad_outside_nonzero"] = int(np.fromfile(f"{d}/grad_outside_nonzero.bin", np.uint64)[0])
+        if recompute:
+            res["grad_recompute"] = np.fromfile(f"{d}/grad_recompute.bin", np.float32).reshape(n, n, n, 4)
         if noalloc:
             res["grad_noalloc"] = np.fromfile(f"{d}/grad_noalloc.bin", np.float32).reshape(n, n, n, 4)
     if shade is not None:

@@ -225,6 +225,11 @@ bool try_complete_barrier() {
 
 }  // namespace
 
+int emu_split_tiles(int library) {
+    const char* v = getenv("VCT_EMU_SPLIT_TILES");
+    return v ? atoi(v) : library;
+}
+
 EmuDim emu_thread_idx() { return g_cur->tid; }
 
 void emu_shutdown() {

@@ -144,6 +144,11 @@ void emu_check_acc(uint64_t idx, const char* site);
 #define VCT_CHECK_TEXEL(idx) emu_check_texel((uint64_t)(idx), EMU_SITE)
 #define VCT_CHECK_ACC(idx) emu_check_acc((uint64_t)(idx), EMU_SITE)
 
+// ---- dispatch by frame size: the library's limits, or VCT_EMU_SPLIT_TILES of the environment for both
+int emu_split_tiles(int library);
+#define VCT_SPLIT_FORWARD_TILES emu_split_tiles(768)
+#define VCT_SPLIT_SCATTER_TILES emu_split_tiles(4096)
+
 // ---- launches
 void emu_run_grid(dim3 grid, dim3 block, void (*body)(void*), void* ctx);
 template <typename F, typename... A>

@@ -261,6 +261,12 @@ int main(int argc, char** argv) {
             write_file("grad_outside_nonzero.bin", &outside, sizeof outside);
         }
         fprintf(stderr, "backward done\n");
+        if ((int)num("recompute", 0.0)) {
+            Buf grad3(nvox * 16, "grad_base (recomputing)"), ws3(ws_bytes, "workspace (recomputing)");
+            check(vct_trace_backward(&g, pyr.p, &gb, &p, gout.as<float>(), grad3.as<float>(), ws3.p, ws3.n, nullptr),
+                  "vct_trace_backward");
+            write_file("grad_recompute.bin", grad3.p, grad3.n);
+        }
         if ((int)num("noalloc", 0.0)) {
             Buf grad2(nvox * 16, "grad_base (allocation-free)");
             check(vct_trace_backward_saved_noalloc(&g, pyr.p, &gb, &p, state.p, state.n, gout.as<float>(),
