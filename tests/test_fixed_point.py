@@ -8,8 +8,8 @@ import pytest
 from tests.test_host_emulation import CLANG, CSRC, EMU, ROOT
 
 
-def run_program(tmp_path, source):
-    """Compile one host program of tests/hostemu with the kernels' headers and run it."""
+def run_program(tmp_path, source, *more):
+    """Compile one host program of tests/hostemu (and more sources beside it) with the kernels' headers and run it."""
     if not os.path.exists(CLANG):
         pytest.skip("ROCm clang++ is not installed")
     exe = str(tmp_path / "program")
@@ -17,7 +17,7 @@ def run_program(tmp_path, source):
     cmd = [CLANG, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-DVCT_HOST_EMULATION", "-I/opt/rocm/include",
            f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}", f"-I{EMU}", "-include", "emu.h", "-include", "cfloat",
            "-fsanitize=undefined,float-cast-overflow", "-fno-sanitize-recover=all", "-Wno-unused-value",
-           "-Wno-unused-function", os.path.join(EMU, source), "-o", exe]
+           "-Wno-unused-function", *(os.path.join(EMU, f) for f in (source, *more)), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
