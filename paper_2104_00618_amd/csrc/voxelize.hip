@@ -34,15 +34,20 @@
 // raster pass runs, the alpha word of a reached voxel in `base` holds the
 // index + 1 of its accumulator slot: that of the first fragment's pixel in the
 // flattened pixel space, put there by a compare-and-swap.  Only when that space
-// has more pixels than the grid has voxels, and so than there are slots, are slots
-// taken from a counter (a compare-and-swap to a claim mark, then the index is
+// has more pixels than there are slots (one per voxel, less 1 in 257 for the
+// bits below) are slots taken from a counter (a compare-and-swap to a claim mark, then the index is
 // published; fragments that find the mark read the word again until the index
 // appears, which follows the claim directly).  A slot is {int64
 // r, g, b; uint32 count; uint32 voxel + 1} (32 bytes), and with surface
 // attributes {int64 nx, ny, nz, r, g, b} (48 bytes) more.  Only as many slots
 // as the triangles' bounding boxes hold pixels (at most one per voxel) are
 // cleared, by fill kernels (no memset, so the path can be captured in a
-// graph); the resolve pass walks those slots and writes their voxels.
+// graph); the resolve pass writes the voxels of the used ones.  (Slots named by
+// pixels have gaps, wide ones where triangles fill little of their boxes, so each
+// wave of the raster pass leaves the bits of the slots that its 64 pixels claimed,
+// and the resolve pass reads no others: 200 triangles
+// thinner than a voxel along the diagonals of a 256^3 grid, 6465 of whose 12 million
+// slots are used, 259 -> 214 us; with surface attributes 501 -> 443.)
 // Which slot a voxel gets depends on arrival order; the integer sums in it do
 // not, so the grids are the same bits whatever the order.
 //
@@ -184,8 +189,7 @@ __device__ __forceinline__ unsigned long long tri_setup(const VoxArgs& a, const 
 }
 
 // 16-byte stores of a thread of the clearing pass, 16 KB apart and with no loop: 4096
-// workgroups in a loop cleared a 512^3 base in 48 us more than this, 20 more than
-// 16384 of 256 threads.
+// workgroups in a loop took 65 us longer for a 512^3 base, 16384 of 256 threads 46.
 constexpr int kFillStores = 4;
 
 // Zeroes the output grids (n float4 each; normal and albedo may be null) and the slot
@@ -386,6 +390,15 @@ __device__ __forceinline__ long long find_triangles(const unsigned long long* __
     return lo;
 }
 
+// Slots by pixel: one for each, and behind them one bit for each (whether it is used).
+__device__ __forceinline__ bool slots_by_pixel(unsigned long long total, unsigned int cap) {
+    static_assert(sizeof(VoxAcc) * 8 == 256);
+    return total + (total + 255) / 256 <= cap;
+}
+__device__ __forceinline__ unsigned long long* claim_bits(VoxAcc* acc, unsigned long long total) {
+    return reinterpret_cast<unsigned long long*>(acc + total);
+}
+
 // One lane per bounding-box pixel of the flattened pixel space (triangle t
 // owns [offs[t], offs[t] + npx)), in a grid-stride loop; a lane's triangle is
 // the last t with offs[t] <= g (a triangle without pixels has offs[t] =
@@ -420,7 +433,7 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
     }
     const unsigned long long total = *total_p;
     const unsigned int cap = (unsigned int)a.n * a.n * a.n;
-    const bool direct = total <= cap;
+    const bool direct = slots_by_pixel(total, cap);
     const unsigned long long stride = (unsigned long long)kRasterBlocks * blockDim.x;
     const int32_t h = kSub / 2;
     const float sub_to_world = a.voxel / (float)kSub;
@@ -429,11 +442,11 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
     for (unsigned long long gw = (unsigned long long)block * blockDim.x + (threadIdx.x & ~63u); gw < total; gw += stride) {
         const long long lo = find_triangles(offs, n_tris, gw, lane, s_off + (threadIdx.x & ~63u));
         const unsigned long long g = gw + lane;
-        if (g >= total) continue;
-        const TriSetup& r = setup[lo];
-        const int p = (int)(g - offs[lo]);
-        const long long den = r.nw * kSub;
-        {
+        bool claimed = false;
+        if (g < total) do {
+            const TriSetup& r = setup[lo];
+            const int p = (int)(g - offs[lo]);
+            const long long den = r.nw * kSub;
             const int pj_off = (int)((unsigned)p / (unsigned)r.w);
             const int32_t pi = r.i0 + (p - pj_off * r.w), pj = r.j0 + pj_off;
             const int32_t PX = pi * kSub + h, PY = pj * kSub + h;
@@ -443,11 +456,11 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
             const bool in = (ea > 0 || (ea == 0 && top_left(r.B[0] - r.A[0], r.B[1] - r.A[1]))) &&
                             (eb > 0 || (eb == 0 && top_left(r.C[0] - r.B[0], r.C[1] - r.B[1]))) &&
                             (ec > 0 || (ec == 0 && top_left(r.A[0] - r.C[0], r.A[1] - r.C[1])));
-            if (!in) continue;
+            if (!in) break;
             const long long wnum = r.nw * r.A[2] - r.nx * (PX - r.A[0]) - r.ny * (PY - r.A[1]);
-            if (wnum < 0) continue;                                  // depth below the grid
+            if (wnum < 0) break;                                  // depth below the grid
             const long long layer = floor_div_est(wnum, den);
-            if (layer >= a.n) continue;
+            if (layer >= a.n) break;
             const int32_t lay = (int32_t)layer;
             const int32_t v[3] = {r.dom == 0 ? lay : pi, r.dom == 0 ? pj : r.dom == 1 ? lay : pj, r.dom == 0 ? pi : r.dom == 1 ? pj : lay};
             const float fx = (float)PX, fy = (float)PY, fw = (float)wnum / (float)r.nw;
@@ -477,6 +490,7 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
                 s = atomicCAS(word, 0u, (unsigned int)g + 1u);
                 if (s == 0u) {
                     s = (unsigned int)g + 1u;
+                    claimed = true;
                     acc[g].voxel = vi + 1u;   // read by the resolve pass only
                 }
             } else if (s == 0u) {
@@ -491,7 +505,7 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
             if (!direct)
                 for (int spin = 0; s == kClaimed && spin < kMaxSpin; ++spin)
                     s = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (s > cap) continue;   // (not reached: see above; a claim is published right away)
+            if (s > cap) break;   // (not reached: see above; a claim is published right away)
             VoxAcc* q = acc + (s - 1u);
             atomicAdd(&q->r, to_fixed(lr * r.col[0]));
             atomicAdd(&q->g, to_fixed(lg * r.col[1]));
@@ -504,33 +518,49 @@ __global__ __launch_bounds__(256) void k_raster(VoxArgs a, const TriSetup* __res
                     atomicAdd(&u->c[i], to_fixed(r.col[i]));
                 }
             }
+        } while (false);
+        if (direct) {
+            const unsigned long long bits = __ballot(claimed);
+            if (lane == 0) claim_bits(acc, total)[gw >> 6] = bits;
         }
     }
 }
 
-// One thread per used slot: write its voxel in the output grids (the other
-// voxels keep the zeros of k_clear and of the raster launch's fill).
+// One thread per slot: writes the voxels of the used ones in the output grids (the
+// others keep the zeros of k_begin and of the raster launch's fill).
 template <bool SURF>
-__global__ __launch_bounds__(256) void k_resolve(const VoxAcc* __restrict__ acc, const SurfAcc* __restrict__ surf,
+__global__ __launch_bounds__(256) void k_resolve(VoxAcc* __restrict__ acc, const SurfAcc* __restrict__ surf,
                                                  const unsigned int* __restrict__ counter,
                                                  const unsigned long long* __restrict__ total_p, unsigned int cap,
                                                  float4* __restrict__ base,
                                                  float4* __restrict__ normal, float4* __restrict__ albedo) {
     const unsigned long long total = *total_p;
-    const unsigned int used = total <= cap ? (unsigned int)total : min(*counter, cap);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < used; i += (size_t)gridDim.x * blockDim.x) {
-        const VoxAcc q = acc[i];
-        if (q.voxel == 0u) continue;
-        const size_t v = (size_t)q.voxel - 1u;
-        const float inv = 1.0f / ((float)q.count * kFix);
-        base[v] = make_float4((float)(long long)q.r * inv, (float)(long long)q.g * inv, (float)(long long)q.b * inv,
-                              1.0f);
-        if constexpr (SURF) {
-            const SurfAcc u = surf[i];
-            normal[v] = make_float4((float)(long long)u.n[0] * inv, (float)(long long)u.n[1] * inv,
-                                    (float)(long long)u.n[2] * inv, 1.0f);
-            albedo[v] = make_float4((float)(long long)u.c[0] * inv, (float)(long long)u.c[1] * inv,
-                                    (float)(long long)u.c[2] * inv, 1.0f);
+    const bool direct = slots_by_pixel(total, cap);
+    const unsigned int used = direct ? (unsigned int)total : min(*counter, cap);
+    const unsigned long long* bits = claim_bits(acc, total);
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    constexpr int kAhead = 4;   // slots whose bits a thread reads at a time
+    for (size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i0 < used; i0 += kAhead * stride) {
+        unsigned long long word[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) word[k] = !direct ? ~0ull : i0 + k * stride < used ? bits[(i0 + k * stride) >> 6] : 0ull;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const size_t i = i0 + k * stride;
+            if (i >= used || !(word[k] >> (i & 63) & 1ull)) continue;
+            const VoxAcc q = acc[i];
+            if (q.voxel == 0u) continue;
+            const size_t v = (size_t)q.voxel - 1u;
+            const float inv = 1.0f / ((float)q.count * kFix);
+            base[v] = make_float4((float)(long long)q.r * inv, (float)(long long)q.g * inv, (float)(long long)q.b * inv,
+                                  1.0f);
+            if constexpr (SURF) {
+                const SurfAcc u = surf[i];
+                normal[v] = make_float4((float)(long long)u.n[0] * inv, (float)(long long)u.n[1] * inv,
+                                        (float)(long long)u.n[2] * inv, 1.0f);
+                albedo[v] = make_float4((float)(long long)u.c[0] * inv, (float)(long long)u.c[1] * inv,
+                                        (float)(long long)u.c[2] * inv, 1.0f);
+            }
         }
     }
 }
