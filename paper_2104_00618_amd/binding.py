@@ -243,17 +243,17 @@ def voxelize_params(lights, ambient=0.1, diffuse=1.0):
     return c
 
 
-def _rows(v):
-    """v as something that iterates fast (an array's or a tensor's elements one by one do not)."""
-    return v.tolist() if isinstance(v, (np.ndarray, torch.Tensor)) else v
+def _rows(v, dims):
+    """v as something that iterates fast (the elements of an array or a tensor, here of so many dimensions, do not)."""
+    return v.tolist() if isinstance(v, (np.ndarray, torch.Tensor)) and v.ndim == dims else v
 
 
 def cone_params(p):
     """C struct from any object with the cone-set attributes (n_diffuse taken
     from len(diffuse_dirs))."""
     c = CConeParams()
-    dirs = [tuple(map(float, d)) for d in _rows(p.diffuse_dirs)]
-    wts = [float(w) for w in _rows(p.diffuse_weights)]
+    dirs = [tuple(map(float, d)) for d in _rows(p.diffuse_dirs, 2)]
+    wts = [float(w) for w in _rows(p.diffuse_weights, 1)]
     if len(dirs) > MAX_DIFFUSE or len(wts) != len(dirs):
         raise ValueError("diffuse_dirs / diffuse_weights: at most 16 cones, one weight per direction")
     c.n_diffuse = len(dirs)
