@@ -538,14 +538,20 @@ __device__ __forceinline__ void emit_dirs(const Scatter& t, const TraceArgs& a, 
 // 371 -> 147, 128 x 128 320 -> 179, 192 x 192 (576) 274 -> 205; 256 x 256 (1024) would
 // go 266 -> 261, and 529 -> 563 with an anisotropic pyramid.
 constexpr int kPartLog = 1;
+// Only the cones that are switched on get workgroups (others would clear their table for
+// nothing), and one cone alone is spread over parts or not at all: a diffuse cone at
+// 700 x 700, 64^3, took 174 us with workgroups for the two that are off, now 147.
 struct SplitPlan {
-    int32_t spec, others;   // waves for each specular cone and for each other cone (powers of two); 0: no split
+    int32_t spec, others;   // waves for each specular cone (0: none) and for each other cone (powers of two); others 0: no split
 };
 SplitPlan split_plan(const TraceArgs& a) {
+    const int cones = vct_cones(a);
     const int64_t waves = (int64_t)tiles8(a).n * (a.n_diffuse + 2);
     const int64_t r = 20480 / (waves > 0 ? waves : 1);
-    if (r < 4) return {1, 1};
-    return r >= 16 ? SplitPlan{16, 4} : r >= 8 ? SplitPlan{8, 4} : SplitPlan{4, 2};
+    if (!vct_split_scatter(a) || cones == 0 || (cones == 1 && r < 4)) return {0, 0};
+    SplitPlan p = r < 4 ? SplitPlan{1, 1} : r >= 16 ? SplitPlan{16, 4} : r >= 8 ? SplitPlan{8, 4} : SplitPlan{4, 2};
+    if (!a.enable_spec) p.spec = 0;
+    return p;
 }
 
 constexpr int kSmallMax = 704;        // texels of all levels with side <= 8 (8^3 + 3 bricks of 64)
@@ -571,17 +577,23 @@ __global__ __launch_bounds__(kThreads, 4) void k_bwd_pass2(TraceArgs a, const fl
     // frames (Tile8), one cone of an 8x8 tile (four tiles a workgroup, the
     // specular cones first: the longest), of which it emits one part's samples
     int view, y, x, slot0 = 0, slot1 = a.n_diffuse + 2, part = 0, part_mask = 0;
-    if (split.spec) {
+    if (split.others) {
         const Tile8 tl = tiles8(a);
         const int groups = (tl.n + 3) >> 2;
-        int item = (int)blockIdx.x / groups;
+        int item = (int)blockIdx.x / groups;   // specular parts, then those of occlusion and of the diffuse cones
         const int tile = xcd_tile((int)blockIdx.x - item * groups, groups) * 4 + (int)(threadIdx.x >> 6);
         tile8_pixel(tl, min(tile, tl.n - 1), lane, view, y, x);
         if (tile >= tl.n) x = a.w;   // (the last group's surplus waves have no pixels)
-        part_mask = (item < split.spec ? split.spec : split.others) - 1;
-        if (item >= split.spec) item += split.others - split.spec;
+        if (item < split.spec) {
+            part_mask = split.spec - 1;
+            slot0 = a.n_diffuse;
+        } else {
+            item -= split.spec;
+            part_mask = split.others - 1;
+            const int c = item / split.others - a.enable_occ;
+            slot0 = c < 0 ? a.n_diffuse + 1 : c;
+        }
         part = item & part_mask;
-        slot0 = item_slot(a, item / (part_mask + 1));
         slot1 = slot0 + 1;
     } else {
         tile_pixel(a, xcd_tile(blockIdx.x, a.n_tiles), threadIdx.x, view, y, x);
@@ -858,7 +870,7 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
     hipLaunchKernelGGL(k_fill_zero, dim3(fb), dim3(256), 0, s, reinterpret_cast<uint4*>(acc), n16);
     const float4* g4 = reinterpret_cast<const float4*>(grad_out);
     es.mark(s);
-    const bool split_march = !saved && vct_split_forward(a), split = vct_split_scatter(a);
+    const bool split_march = !saved && vct_split_forward(a);
     if (a.n_tiles > 0) {
         if (split_march)
             hipLaunchKernelGGL((k_trace_save_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, s, a, nullptr,
@@ -884,12 +896,8 @@ hipError_t run_backward(const PyrLayout& L, const TraceArgs& a, const BackwardPl
     if (small_n > (ANISO ? kSmallMaxAniso : kSmallMax)) return hipErrorInvalidValue;
     es.mark(s);
     if (a.n_tiles > 0) {
-        SplitPlan sp = {0, 0};
-        int blocks = a.n_tiles;
-        if (split) {
-            sp = split_plan(a);
-            blocks = (tiles8(a).n + 3) / 4 * (sp.spec + sp.others * (a.n_diffuse + 1));
-        }
+        const SplitPlan sp = split_plan(a);
+        const int blocks = sp.others ? (tiles8(a).n + 3) / 4 * (sp.spec + sp.others * (a.n_diffuse + a.enable_occ)) : a.n_tiles;
         hipLaunchKernelGGL((k_bwd_pass2<DT, ANISO>), dim3(blocks), dim3(kThreads), 0, s, a, g4, state, ctl, acc,
                            small_off, small_n, sp);
     }

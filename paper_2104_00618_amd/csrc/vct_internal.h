@@ -162,6 +162,8 @@ struct TraceArgs {
 #define VCT_SPLIT_FORWARD_TILES 768
 #define VCT_SPLIT_SCATTER_TILES 4096
 #endif
+// Cones of a pixel that are switched on.
+static inline int vct_cones(const TraceArgs& a) { return a.n_diffuse + a.enable_spec + a.enable_occ; }
 static inline bool vct_split_forward(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_FORWARD_TILES; }
 static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_SCATTER_TILES; }
 
