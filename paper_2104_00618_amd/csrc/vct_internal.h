@@ -155,12 +155,13 @@ struct TraceArgs {
 // 256 x 256 (256 tiles) trace 102 -> 63 us, saving forward 118 -> 69, shading 90 -> 60;
 // even at 512 x 512 (1024), and 633 -> 719 us for the trace at 1280 x 720 (3600).
 // The scatter pass has nothing to join, and its longer chains gain up to larger
-// frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1951 -> 1864 at 1280 x 720,
-// 4594 -> 4637 at 1920 x 1080 (8160).
+// frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1674 -> 1493 at 1280 x 720
+// (3600; 984 -> 951 at 16^3), 2407 -> 2312 for 4 x 512 x 512 (4096), but there 1133 -> 1230 at
+// 16^3, whose samples are nearly all in the table that each workgroup clears and flushes.
 // (The limits are hooks: a host-emulation build runs either kernel on any frame.)
 #ifndef VCT_SPLIT_FORWARD_TILES
 #define VCT_SPLIT_FORWARD_TILES 768
-#define VCT_SPLIT_SCATTER_TILES 4096
+#define VCT_SPLIT_SCATTER_TILES 3600
 #endif
 // Cones of a pixel that are switched on.
 static inline int vct_cones(const TraceArgs& a) { return a.n_diffuse + a.enable_spec + a.enable_occ; }

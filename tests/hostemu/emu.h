@@ -147,7 +147,7 @@ void emu_check_acc(uint64_t idx, const char* site);
 // ---- dispatch by frame size: the library's limits, or VCT_EMU_SPLIT_TILES of the environment for both
 int emu_split_tiles(int library);
 #define VCT_SPLIT_FORWARD_TILES emu_split_tiles(768)
-#define VCT_SPLIT_SCATTER_TILES emu_split_tiles(4096)
+#define VCT_SPLIT_SCATTER_TILES emu_split_tiles(3600)
 
 // ---- launches
 void emu_run_grid(dim3 grid, dim3 block, void (*body)(void*), void* ctx);
