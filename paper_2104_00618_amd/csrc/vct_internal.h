@@ -151,9 +151,11 @@ struct TraceArgs {
 
 // Frames whose cones are spread over waves of their own (Tile8 in march.h), by
 // their 16x16-pixel tiles.  The forward kernels join a tile's cones at the end, so
-// they gain while one wave per 64 pixels leaves SIMDs short of waves: at 64^3 /
-// 256 x 256 (256 tiles) trace 102 -> 63 us, saving forward 118 -> 69, shading 90 -> 60;
-// even at 512 x 512 (1024), and 633 -> 719 us for the trace at 1280 x 720 (3600).
+// they gain while one wave per 64 pixels leaves SIMDs short of waves, and the longer
+// the more cones there are to spread: trace of eight at 64^3 / 256 x 256 (256 tiles) 102 ->
+// 63 us, saving forward 118 -> 69, even at 512 x 512 (1024), and 633 -> 719 us at 1280 x
+// 720 (3600); of six at 432 x 432 (729) 100 -> 111, gaining at 360 x 360 (529); of three at
+// 256 x 256 and float16 58 -> 69, gaining at 128 x 128 (64).
 // The scatter pass has nothing to join, and its longer chains gain up to larger
 // frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1674 -> 1493 at 1280 x 720
 // (3600; 984 -> 951 at 16^3), 2407 -> 2312 for 4 x 512 x 512 (4096), but there 1133 -> 1230 at
@@ -165,7 +167,10 @@ struct TraceArgs {
 #endif
 // Cones of a pixel that are switched on.
 static inline int vct_cones(const TraceArgs& a) { return a.n_diffuse + a.enable_spec + a.enable_occ; }
-static inline bool vct_split_forward(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_FORWARD_TILES; }
+static inline bool vct_split_forward(const TraceArgs& a) {
+    const int most = 110 * (vct_cones(a) - 1);
+    return a.n_tiles <= (most < VCT_SPLIT_FORWARD_TILES ? most : VCT_SPLIT_FORWARD_TILES);
+}
 static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_SCATTER_TILES; }
 
 // Calls f(std::integral_constant<int, DT>) with the kernel template argument
