@@ -53,7 +53,15 @@ __global__ __launch_bounds__(256) void k_shade(TraceArgs a, ShadeArgs s, float4*
 }
 
 // The shading of small frames (Tile8 in march.h): items are the specular cone,
-// the lights' occlusion cones, then the diffuse cones.
+// the lights' occlusion cones, then the diffuse cones.  First-hit cones and faded occlusion
+// cones are shorter than a trace's, so the specular one soon is all the time, and
+// frames gain up to 256 tiles only (256 x 256: 94 -> 70 us at 64^3 with six cones and two
+// lights, 72 -> 71 with five and one in float16; 360 x 360: 109 -> 107 and 93 -> 102).  Directional
+// float32 pyramids are marched slower from here, by half on some frames (64^3, 8 x 32 x 32,
+// five and one: 163 -> 184 us; 256^3, 256 x 256: 202 -> 277), and keep one lane a pixel.
+template <int DT, bool ANISO>
+constexpr bool kShadeSplit = !(ANISO && (DT & ~VCT_WIDE) == VCT_F32);
+constexpr int kShadeSplitTiles = 256;
 template <int DT, bool ANISO>
 __global__ __launch_bounds__(64 * kSplitWaves, 4) void k_shade_split(TraceArgs a, ShadeArgs s, float4* __restrict__ out) {
     __shared__ LevelTable T;
@@ -123,10 +131,12 @@ template <int DT, bool ANISO>
 void launch_shade(const TraceArgs& a, const ShadeArgs& s, float* out, unsigned long long* count, hipStream_t st) {
     if (count)
         hipLaunchKernelGGL((k_shade<DT, ANISO, true>), dim3(a.n_tiles), dim3(256), 0, st, a, s, nullptr, count);
-    else if (vct_split_forward(a))
-        hipLaunchKernelGGL((k_shade_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, st, a, s,
-                           reinterpret_cast<float4*>(out));
-    else
+    else if (kShadeSplit<DT, ANISO> && a.n_tiles <= min(VCT_SPLIT_FORWARD_TILES, kShadeSplitTiles) &&
+             s.n_lights + a.n_diffuse > 0) {
+        if constexpr (kShadeSplit<DT, ANISO>)
+            hipLaunchKernelGGL((k_shade_split<DT, ANISO>), dim3(tiles8(a).n), dim3(64 * kSplitWaves), 0, st, a, s,
+                               reinterpret_cast<float4*>(out));
+    } else
         hipLaunchKernelGGL((k_shade<DT, ANISO, false>), dim3(a.n_tiles), dim3(256), 0, st, a, s,
                            reinterpret_cast<float4*>(out), nullptr);
 }
