@@ -241,20 +241,7 @@ __device__ __forceinline__ void trace_save_pixel(const TraceArgs& a, const Level
             Cone c = cone_for_slot<true>(a, P, slot, cam);
             Pass1Out r = pass1_march<DT, ANISO>(a, T, c, D);
             out = lane_state(r);
-            const float cr = r.C[0].hi + r.C[0].lo, cg = r.C[1].hi + r.C[1].lo, cb = r.C[2].hi + r.C[2].lo;
-            if (slot < a.n_diffuse) {
-                const float wq = a.weight[slot];
-                o0.x = __builtin_fmaf(wq, cr, o0.x);
-                o0.y = __builtin_fmaf(wq, cg, o0.y);
-                o0.z = __builtin_fmaf(wq, cb, o0.z);
-                o0.w = __builtin_fmaf(wq, r.A, o0.w);
-            } else if (slot == a.n_diffuse) {
-                o1.x = cr;
-                o1.y = cg;
-                o1.z = cb;
-            } else {
-                o1.w = r.A;
-            }
+            add_slot(a, slot, r.C[0].hi + r.C[0].lo, r.C[1].hi + r.C[1].lo, r.C[2].hi + r.C[2].lo, r.A, o0, o1);
         }
         lane_put(a, state, pix, slot, out);
     }

@@ -606,27 +606,21 @@ __device__ __forceinline__ void trace_pixel(const TraceArgs& a, const LevelTable
     for (int q = 0; q < a.n_diffuse; ++q) {
         Cone c = cone_for_slot(a, P, q, cam);
         MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, c, D);
-        float wq = a.weight[q];
-        o0.x = __builtin_fmaf(wq, m.r, o0.x);
-        o0.y = __builtin_fmaf(wq, m.g, o0.y);
-        o0.z = __builtin_fmaf(wq, m.b, o0.z);
-        o0.w = __builtin_fmaf(wq, m.a, o0.w);
+        add_slot(a, q, m.r, m.g, m.b, m.a, o0, o1);
         ksum += m.k;
         k2sum += m.k2;
     }
     if (a.enable_spec) {
         Cone c = cone_for_slot(a, P, a.n_diffuse, cam);
         MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, c, D);
-        o1.x = m.r;
-        o1.y = m.g;
-        o1.z = m.b;
+        add_slot(a, a.n_diffuse, m.r, m.g, m.b, m.a, o0, o1);
         ksum += m.k;
         k2sum += m.k2;
     }
     if (a.enable_occ) {
         Cone c = cone_for_slot(a, P, a.n_diffuse + 1, cam);
         MarchResult m = march<DT, ANISO, kShareFootprint<DT>>(a, T, c, D);
-        o1.w = m.a;
+        add_slot(a, a.n_diffuse + 1, m.r, m.g, m.b, m.a, o0, o1);
         ksum += m.k;
         k2sum += m.k2;
     }

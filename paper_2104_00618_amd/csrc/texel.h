@@ -65,13 +65,11 @@ __device__ vct_v4f vct_struct_load_v4f32(vct_v4i rsrc, int32_t vindex, int32_t v
                                          int32_t aux) __asm("llvm.amdgcn.struct.buffer.load.v4f32");
 __device__ vct_v2i vct_struct_load_v2i32(vct_v4i rsrc, int32_t vindex, int32_t voffset, int32_t soffset,
                                          int32_t aux) __asm("llvm.amdgcn.struct.buffer.load.v2i32");
-// s_buffer_load_dwordx4 / _dwordx2 (byte offset): a read whose resource and
+// s_buffer_load_dwordx4 (byte offset): a read whose resource and
 // offset are the same in every lane of the wave, through the scalar data
 // cache into scalar registers; dwords past the resource's range read as zero.
 __device__ vct_v4i vct_scalar_load_v4i32(vct_v4i rsrc, int32_t offset,
                                          int32_t aux) __asm("llvm.amdgcn.s.buffer.load.v4i32");
-__device__ vct_v2i vct_scalar_load_v2i32(vct_v4i rsrc, int32_t offset,
-                                         int32_t aux) __asm("llvm.amdgcn.s.buffer.load.v2i32");
 #else
 // host-side verification builds supply these
 vct_v4i vct_raw_load_v4i32(vct_v4i rsrc, int32_t voffset, int32_t soffset, int32_t aux);
@@ -79,7 +77,6 @@ vct_v2i vct_raw_load_v2i32(vct_v4i rsrc, int32_t voffset, int32_t soffset, int32
 vct_v4f vct_struct_load_v4f32(vct_v4i rsrc, int32_t vindex, int32_t voffset, int32_t soffset, int32_t aux);
 vct_v2i vct_struct_load_v2i32(vct_v4i rsrc, int32_t vindex, int32_t voffset, int32_t soffset, int32_t aux);
 vct_v4i vct_scalar_load_v4i32(vct_v4i rsrc, int32_t offset, int32_t aux);
-vct_v2i vct_scalar_load_v2i32(vct_v4i rsrc, int32_t offset, int32_t aux);
 #endif
 
 // float16 / bfloat16 texel from its two 32-bit words (the decode of vct_fetch_texel).

@@ -436,13 +436,6 @@ vct_v4i vct_scalar_load_v4i32(vct_v4i rsrc, int32_t offset, int32_t) {
     v.x = o[0], v.y = o[1], v.z = o[2], v.w = o[3];
     return v;
 }
-vct_v2i vct_scalar_load_v2i32(vct_v4i rsrc, int32_t offset, int32_t) {
-    vct_v2i v;
-    int32_t o[2];
-    raw_load<2>(rsrc, (uint32_t)offset, o, "scalar dwordx2");
-    v.x = o[0], v.y = o[1];
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // the few HIP runtime calls the library's host code makes
