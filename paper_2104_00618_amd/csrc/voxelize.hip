@@ -109,8 +109,7 @@ struct TriSetup {
     float n[3], col[3];
     int32_t dom;                     // source axis of W (its X2, Y2 | W: z, y | x; x, z | y; x, y | z)
 };
-constexpr size_t kSetupBytes = 152;  // workspace bytes for each
-static_assert(sizeof(TriSetup) <= kSetupBytes);
+static_assert(sizeof(TriSetup) == 104);
 
 constexpr int kScanBlock = 1024;     // counts per block of the offset scan (256 threads x 4)
 constexpr int kScanThreads = 1024;   // threads of the one-workgroup scan of block sums
@@ -572,7 +571,7 @@ size_t vct_voxelize_acc_bytes(int n, bool surface) {
 }
 
 size_t vct_voxelize_workspace_size(int n, long long n_tris, bool surface) {
-    return vct_voxelize_acc_bytes(n, surface) + (size_t)n_tris * (kSetupBytes + 8) + 256 +
+    return vct_voxelize_acc_bytes(n, surface) + (size_t)n_tris * (sizeof(TriSetup) + 8) + 256 +
            (size_t)((n_tris + kScanBlock - 1) / kScanBlock) * 8;
 }
 
