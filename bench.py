@@ -712,7 +712,7 @@ def main():
                          model=f"{FLOPS_FWD[2]} FP32 ops per cone sample (every sample counted as two-level; the "
                                f"per-light terms are left out) x {shade_samples} samples (vct_count_shade_samples, "
                                f"3 lights, the thesis's variants)"),
-        "f2_voxelize": {"kernel": "k_clear + k_tri_setup + offset scan + k_clear_slots + k_raster + k_resolve",
+        "f2_voxelize": {"kernel": "k_begin + offset scan + k_offsets_slots + k_raster + k_resolve",
                         "ms": vox_ms, "bound": "hbm", "achieved": vox_bytes / (vox_ms * 1e-3) / 1e9,
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": vox_bytes / (vox_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                         "model": f"16 B per voxel: the light grid written once ({vox_bytes} bytes); accumulators "

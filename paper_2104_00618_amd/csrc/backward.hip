@@ -8,8 +8,9 @@
 // (derivatives of the front-to-back recurrences of Section 4.3.2).  While a
 // cone continues, A_{k+1} < alpha_thresh, so T_{k+1} > 1 - alpha_thresh and,
 // since T is computed as 1 - A in float32, T_{k+1} >= 2^-24 in any case.
-// C is accumulated as a double-float in both passes so that C_K - C_{k+1} is
-// accurate to ~1e-14 of C_K.
+// C_K is accumulated as a double-float and the samples are taken off it again in the
+// re-march, so that C_K - C_{k+1} is accurate to ~1e-14 of C_K.  All this needs
+// the re-march to take the forward's samples bit for bit (pass2_init).
 //
 // Deterministic reduction: every tap contribution g * w is converted to a
 // 64-bit fixed-point integer with a per-call power-of-two scale 2^E (level l
@@ -439,8 +440,8 @@ __device__ __forceinline__ void emit_level_dirs(const Scatter& t, bool live, con
 // uniform in a group), once for the three directions; each group then runs
 // one butterfly per axis, with the lane's gradient scaled by its w_a^2 for
 // that axis, and adds the sum at that direction's offset.  (Grouping once in
-// place of once per direction: the group loop, the slot-order weights and the
-// clamp key are shared by the three.)
+// place of once per direction: the group loop and the slot-order weights are
+// shared by the three.)
 template <bool ALPHA_ONLY>
 __device__ __forceinline__ void emit_level_axes(const Scatter& t, bool live, const LevelGeom& geo, float wl,
                                                 const float gs[4], const EmitLane& e, const float wt[3], int sgn,

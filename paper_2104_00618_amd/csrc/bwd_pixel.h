@@ -248,9 +248,8 @@ __device__ __forceinline__ void trace_save_pixel(const TraceArgs& a, const Level
 }
 
 // Pass-2 state of one cone of one lane.  (R in place of C_K and C_k: 6 registers and 9
-// instructions a sample fewer.  With it, the fixed point's two signed words and
-// footprints known by their base texel alone, the scatter pass went 4.95 -> 4.75 ms at
-// 1080p / 256^3, 9.81 -> 9.37 ms anisotropic.)
+// instructions a sample fewer.  With it and footprints known by their base texel
+// alone, a training pass at 1080p / 256^3 is 1.05 times as fast, also a directional one.)
 struct Pass2Lane {
     Cone c;
     df R[3];      // C_K - C_k: what the samples still to come add

@@ -101,7 +101,7 @@ __device__ __forceinline__ unsigned long long to_fixed(float v) {
 
 // Rasterization setup of one triangle: snapped, swizzled vertices (counter-
 // clockwise), plane coefficients, pixel bounding box, the unit normal of the
-// original triangle and its colour.  npx = 0 when the triangle produces nothing.
+// original triangle and its colour.
 struct TriSetup {
     int32_t A[3], B[3], C[3];        // (X2, Y2, W) subpixel coordinates
     int32_t i0, j0, w;               // bounding box origin and width in pixels
@@ -302,8 +302,8 @@ __global__ __launch_bounds__(256) void k_offsets_slots(unsigned long long* __res
 }
 
 // The whole offset scan in one workgroup, for meshes of at most kScanSmall
-// triangles (1024 threads x 4 counts): one launch in place of the three of
-// the blocked scan, with the same integer sums.
+// triangles (1024 threads x 4 counts), with the same integer sums as the blocked
+// scan of larger ones.
 constexpr int kScanSmall = 4096;
 __global__ __launch_bounds__(1024) void k_scan_small(unsigned long long* __restrict__ c, long long n,
                                                      unsigned long long* __restrict__ total) {
@@ -399,7 +399,7 @@ __device__ __forceinline__ unsigned long long* claim_bits(VoxAcc* acc, unsigned 
 }
 
 // One lane per bounding-box pixel of the flattened pixel space (triangle t
-// owns [offs[t], offs[t] + npx)), in a grid-stride loop; a lane's triangle is
+// owns the pixels of its box from offs[t] on), in a grid-stride loop; a lane's triangle is
 // the last t with offs[t] <= g (a triangle without pixels has offs[t] =
 // offs[t + 1] and is passed over).
 //
