@@ -434,17 +434,13 @@ __device__ __forceinline__ void pass2_step(const TraceArgs& a, const LevelTable&
 // round(v * 2^e) as a 64-bit integer, exactly; 0 where |v * 2^e| is 2^62 or more or v
 // is not a number, which the scale rules out for sums that the bound counted (float32
 // ops only: the float64 units of gfx950 run at a fraction of the float32 rate).
-// Split at the nearest multiple of 2^32, so that both words convert exactly as
-// signed 32-bit integers, with no sign and carry handling; the low one of a tie
-// is the one below, since +2^31 is no 32-bit integer.
+// The significand of the rounded product becomes the upper word, from where a shift
+// takes the whole number into place: no sign, carry or tie to see to.
 __device__ __forceinline__ long long fixed_point(float v, int e) {
     float x = rintf(ldexpf(v, e));
     x = fabsf(x) < 0x1p62f ? x : 0.0f;
-    const float hi = rintf(x * 0x1p-32f);
-    const float lo = __builtin_fmaf(hi, -0x1p32f, x);
-    const bool tie = lo == 0x1p31f;
-    const int l = (int)(tie ? -lo : lo);
-    return (long long)(((unsigned long long)((uint32_t)(int)hi + (uint32_t)(l >> 31) + (tie ? 1u : 0u)) << 32) | (uint32_t)l);
+    const uint32_t upper = (uint32_t)(int)(__builtin_amdgcn_frexp_mantf(x) * 0x1p31f);   // below 2^31
+    return (long long)((unsigned long long)upper << 32) >> (63 - __builtin_amdgcn_frexp_expf(x));
 }
 
 }  // namespace vct

@@ -105,6 +105,10 @@ inline EmuPair emu_permlane_swap(EmuOp op, uint32_t a, uint32_t b) {
 inline float emu_fmed3f(float a, float b, float c) { return fmaxf(fminf(a, b), fminf(fmaxf(a, b), c)); }
 #define __builtin_amdgcn_fmed3f(a, b, c) emu_fmed3f((a), (b), (c))
 #define __builtin_amdgcn_logf(x) log2f(x)
+inline float emu_frexp_mant(float x) { int e; return frexpf(x, &e); }
+inline int emu_frexp_exp(float x) { int e; frexpf(x, &e); return e; }
+#define __builtin_amdgcn_frexp_mantf(x) emu_frexp_mant(x)
+#define __builtin_amdgcn_frexp_expf(x) emu_frexp_exp(x)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
 #define __popcll(x) __builtin_popcountll(x)
