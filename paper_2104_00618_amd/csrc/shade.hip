@@ -55,13 +55,14 @@ __global__ __launch_bounds__(256) void k_shade(TraceArgs a, ShadeArgs s, float4*
 // The shading of small frames (Tile8 in march.h): items are the specular cone,
 // the lights' occlusion cones, then the diffuse cones.  First-hit cones and faded occlusion
 // cones are shorter than a trace's, so the specular one soon is all the time, and
-// frames gain up to 256 tiles only (256 x 256: 94 -> 70 us at 64^3 with six cones and two
-// lights, 72 -> 71 with five and one in float16; 360 x 360: 109 -> 107 and 93 -> 102).  Directional
+// frames gain up to 400 tiles only (64^3, float16, five cones and one light: 82 -> 73 us at
+// 272 x 256, 93 -> 85 at 400 x 256, 93 -> 102 at 360 x 360, 529 tiles; four and three: 103 ->
+// 74, 112 -> 96; 256^3, a cone and two lights, 400 x 256: 118 -> 122, 113 -> 113 in float16).  Directional
 // float32 pyramids are marched slower from here, by half on some frames (64^3, 8 x 32 x 32,
 // five and one: 163 -> 184 us; 256^3, 256 x 256: 202 -> 277), and keep one lane a pixel.
 template <int DT, bool ANISO>
 constexpr bool kShadeSplit = !(ANISO && (DT & ~VCT_WIDE) == VCT_F32);
-constexpr int kShadeSplitTiles = 256;
+constexpr int kShadeSplitTiles = 400;
 template <int DT, bool ANISO>
 __global__ __launch_bounds__(64 * kSplitWaves, 4) void k_shade_split(TraceArgs a, ShadeArgs s, float4* __restrict__ out) {
     __shared__ LevelTable T;
