@@ -154,13 +154,13 @@ struct TraceArgs {
 // they gain while one wave per 64 pixels leaves SIMDs short of waves, and the longer
 // the more cones there are to spread: trace of eight at 64^3 / 256 x 256 (256 tiles) 102 ->
 // 63 us, saving forward 118 -> 69, even at 512 x 512 (1024), and 633 -> 719 us at 1280 x
-// 720 (3600).  The limits are the last sizes at which the worst of eight frames (64^3 and
-// 256^3, two storage types, isotropic and directional, trace and saving forward) is even:
-// with the specular cone, as long as several others, three cones gain 1.19 to 1.77 times at
-// 144 tiles and 0.84 to 1.53 at 256, five 1.07 to 1.68 at 360 and 0.94 to 1.36 at 441, seven
-// 1.03 to 1.34 at 625; without it the waves share evenly, and two gain 1.18 to 2.0 at 144
-// and 0.93 to 1.79 at 256, three 1.09 to 1.57 at 360, four and six 1.08 to 1.57 at 529 and
-// 0.92 to 1.39 at 625.
+// 720 (3600).  The limits lie where of 16 frames (64^3 and 256^3, two storage types,
+// isotropic and directional, trace and saving forward) about half still gain.  With the
+// specular cone, as long as several others: two cones gain 1.05 to 1.54 times at 144 tiles
+// (0.82 to 1.29 at 360), three 0.84 to 1.57 at 256 (the worst float16; median 1.06 to 1.19;
+// 0.82 at 441), five 0.97 to 1.26 at 529, seven 1.03 to 1.34 at 625.  Without it the waves share
+// evenly, and two gain 1.18 to 2.0 at 144 and 0.93 to 1.79 at 256, three 1.09 to 1.57 at 360, four
+// and six 1.08 to 1.57 at 529 and 0.92 to 1.39 at 625.
 // The scatter pass has nothing to join, and its longer chains gain up to larger
 // frames: 533 -> 260 us at 256 x 256, 1109 -> 799 at 512 x 512, 1674 -> 1493 at 1280 x 720
 // (3600; 984 -> 951 at 16^3), 2407 -> 2312 for 4 x 512 x 512 (4096), but there 1133 -> 1230 at
@@ -174,7 +174,7 @@ struct TraceArgs {
 static inline int vct_cones(const TraceArgs& a) { return a.n_diffuse + a.enable_spec + a.enable_occ; }
 static inline bool vct_split_forward(const TraceArgs& a) {
     const int others = vct_cones(a) - 1;
-    const int most = a.enable_spec ? 110 * others : others < 3 ? 200 * others : 600;
+    const int most = a.enable_spec ? 145 * others : others < 3 ? 200 * others : 600;
     return a.n_tiles <= (most < VCT_SPLIT_FORWARD_TILES ? most : VCT_SPLIT_FORWARD_TILES);
 }
 static inline bool vct_split_scatter(const TraceArgs& a) { return a.n_tiles <= VCT_SPLIT_SCATTER_TILES; }
